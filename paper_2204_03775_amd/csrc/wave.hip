@@ -143,6 +143,9 @@ struct Geo {
 
 }  // namespace
 
+// ints of a context's scale history: a line of exponents, then 4 levels' max slots
+constexpr int kRingInts = kMaxStride + 4 * kMaxSlots * kMaxStride;
+
 // State of the gradient computation (FP32 storage): the checkpoints and the
 // level store of the last checkpointed forward run, the adjoint fields and
 // the FP64 accumulator, all in the field layout (ghost cells zero).
@@ -193,7 +196,7 @@ struct wave_ctx {
     int *rec_start = nullptr;
     long long *rec_off = nullptr;
     int *rec_idx = nullptr;
-    int *ring = nullptr;  // [8]: exps[4] then maxes[4] (16-bit storage)
+    int *ring = nullptr;  // kRingInts: exps[4], padding to a line, then the maxima (16-bit storage)
     // launch configuration
     int variant = 0, zchunk = 0;  // requested (0 = auto)
     int v_used = 0, zc_used = 0;
@@ -504,7 +507,7 @@ StepArgs make_args(const wave_ctx *c)
     a.step = int(c->step & 0x3fffffff);
     a.k_scale = c->k_scale;
     a.exps = c->ring;
-    a.maxes = reinterpret_cast<unsigned *>(c->ring + 4);
+    a.maxes = reinterpret_cast<unsigned *>(c->ring + kMaxStride);
     a.out = c->prev;
     a.grad = nullptr;
     a.aux = nullptr;
@@ -1357,9 +1360,9 @@ int wave_init(wave_ctx **out, const wave_params_t *p, const void *k, void *u_cur
         if (hipMemcpy(c->rec_off_all, off.data(), sizeof(long long) * off.size(), hipMemcpyHostToDevice) != hipSuccess)
             return bail(WAVE_EHIP);
     }
-    if (hipMalloc(&c->ring, 8 * sizeof(int)) != hipSuccess)
+    if (hipMalloc(&c->ring, kRingInts * sizeof(int)) != hipSuccess)
         return bail(WAVE_ENOMEM);
-    if (hipMemsetAsync(c->ring, 0, 8 * sizeof(int), c->stream) != hipSuccess)
+    if (hipMemsetAsync(c->ring, 0, kRingInts * sizeof(int), c->stream) != hipSuccess)
         return bail(WAVE_EHIP);
     plan_launch(c);
     if (build_receiver_tables(c) != WAVE_OK)
@@ -1556,7 +1559,7 @@ int wave_reset(wave_ctx *ctx)
     ctx->cur = ctx->buf0;
     ctx->prev = ctx->buf1;
     ctx->step = 0;
-    HIP_TRY(ctx, hipMemsetAsync(ctx->ring, 0, 8 * sizeof(int), ctx->stream));
+    HIP_TRY(ctx, hipMemsetAsync(ctx->ring, 0, kRingInts * sizeof(int), ctx->stream));
     if (ctx->dbuf)
         HIP_TRY(ctx, hipMemsetAsync(ctx->dbuf, 0, ctx->lay.bytes, ctx->stream));
     return WAVE_OK;

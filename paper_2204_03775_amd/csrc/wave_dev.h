@@ -24,6 +24,11 @@ constexpr double kSymbolMax = 2048.0 / 315.0;
 // largest scaled magnitude a 16-bit field is written with (2^14)
 constexpr int kScaledTopExp = 14;
 
+// slots of a 16-bit level's running maximum, and the ints between two slots
+// (a 128-byte line each); their maximum is the level's
+constexpr int kMaxSlots = 32;
+constexpr int kMaxStride = 32;
+
 constexpr int elem_bytes(int dtype) { return dtype == WAVE_F32 ? 4 : 2; }
 constexpr int kNumKinds = 5;  // storage types WAVE_F32 .. WAVE_BF16_UV
 constexpr bool is_uv(int dtype) { return dtype == WAVE_F16_UV || dtype == WAVE_BF16_UV; }
@@ -64,7 +69,7 @@ struct StepArgs {
     int step;                 // n: this launch writes u^{n+1}
     float k_scale;            // k = stored k * k_scale
     int *exps;                // [4] exponent of u^m in slot m & 3
-    unsigned *maxes;          // [4] max |u^m| (float bits) in slot m & 3
+    unsigned *maxes;          // max |u^m| (float bits): [4][kMaxSlots] slots kMaxStride apart, level m at m & 3
     // output field: == nxt for the in-place step (each cell is read, then
     // written, by the same thread), a separate level otherwise
     void *out;

@@ -245,6 +245,13 @@ struct Scales {
     int e_out;
 };
 
+// slot s of the running maximum of level n (float bits), each on a cache
+// line of its own
+__device__ __forceinline__ unsigned *max_slot(const StepArgs &a, int n, int s)
+{
+    return a.maxes + ((n & 3) * kMaxSlots + s) * kMaxStride;
+}
+
 // The same step in the stored (scaled) units.  With U, P, K the decoded
 // but unscaled u^n, u^{n-1}, k and every scale a power of two, the stored
 // u^{n+1} is
@@ -286,11 +293,20 @@ __device__ __forceinline__ Folded fold_scales(const Coefs &c, const Scales &sc, 
     return f;
 }
 
+// The running maxima of levels n and n - 1 are kept in kMaxSlots slots each
+// (see fold_max): every wave reads one slot per lane, half a wave per level,
+// and reduces them.
 template <int KIND>
 __device__ __forceinline__ Scales step_scales(const StepArgs &a)
 {
+    static_assert(2 * kMaxSlots == 64, "one slot per lane");
     const int n = a.step;
-    const float m = fmaxf(__uint_as_float(a.maxes[n & 3]), __uint_as_float(a.maxes[(n + 3) & 3]));
+    const int lane = threadIdx.x & 63;
+    unsigned mb = *max_slot(a, lane < kMaxSlots ? n : n + 3, lane & (kMaxSlots - 1));
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1)
+        mb = max(mb, (unsigned)__shfl_xor((int)mb, d));
+    const float m = __uint_as_float(__builtin_amdgcn_readfirstlane(mb));
     const float s = a.src_z >= 0 ? fabsf(src_value(a)) : 0.f;
     const float bound = 8.f * m + s;
     int e = 0;
@@ -309,26 +325,42 @@ __device__ __forceinline__ Scales step_scales(const StepArgs &a)
     return sc;
 }
 
-// Publish this step's exponent and clear the max slot the next step fills
-// after this one (slot n + 2, which no launch of this step reads).
+// Publish this step's exponent and clear the max slots the next step fills
+// after this one (level n + 2's, which no launch of this step reads).
 __device__ __forceinline__ void publish_scale(const StepArgs &a, const Scales &sc, int lid, int tid)
 {
-    if (lid == 0 && tid == 0) {
-        a.exps[(a.step + 1) & 3] = sc.e_out;
-        a.maxes[(a.step + 2) & 3] = 0u;
+    if (lid == 0) {
+        if (tid == 0)
+            a.exps[(a.step + 1) & 3] = sc.e_out;
+        if (tid < kMaxSlots)
+            *max_slot(a, a.step + 2, tid) = 0u;
     }
 }
 
-// Fold a per-thread max |u^{n+1}| into the step's slot: a reduction across
-// the wave, then one atomic per wave (on the float bit pattern, valid for
-// non-negative values).
-__device__ __forceinline__ void fold_max(const StepArgs &a, float m)
+// Fold a per-thread max |u^{n+1}| into the level's running maximum: a
+// reduction across each wave, one across the work-group's waves, then one
+// atomic (on the float bit pattern, valid for non-negative values) into slot
+// lid % kMaxSlots.  Atomics on one address from work-groups on 8 XCDs are
+// served one after another in the memory behind the L2s, about 10 ns each,
+// and a launch ends with all of them: one per wave on a single address (2048
+// a launch) took 20 us of the 30 us step of 128^3 FP16 u-and-change and of
+// the 69 us one of 320x288x272 FP16; now 10.4 and 60 us (512^3: 259 -> 250).
+__device__ __forceinline__ void fold_max(const StepArgs &a, int lid, float m)
 {
+    __shared__ float part[16];
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1)
         m = fmaxf(m, __shfl_xor(m, d));
+    const int wave = threadIdx.x >> 6, waves = (blockDim.x + 63) >> 6;
     if ((threadIdx.x & 63) == 0)
-        atomicMax(&a.maxes[(a.step + 1) & 3], __float_as_uint(m));
+        part[wave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < waves; ++w)
+            m = fmaxf(m, part[w]);
+        if (m > 0.f)
+            atomicMax(max_slot(a, a.step + 1, lid & (kMaxSlots - 1)), __float_as_uint(m));
+    }
 }
 
 // Receiver epilogue: after the whole tile column is written, copy the
@@ -850,7 +882,7 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     }
 
     if constexpr (SCALED)
-        fold_max(a, tmax * sc.out);
+        fold_max(a, lid, tmax * sc.out);
     sample_receivers<KIND>(a, lid, tid, NT, sc.out);
 }
 
@@ -1174,7 +1206,7 @@ __global__ __launch_bounds__(256) void step_naive(StepArgs a)
         }
     }
     if constexpr (SCALED)
-        fold_max(a, amax * sc.out);
+        fold_max(a, blockIdx.x, amax * sc.out);
 }
 
 // Receivers for the naive kernel (separate launch: it has no tile
