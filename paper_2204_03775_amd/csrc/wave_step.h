@@ -146,6 +146,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *field, 
                                              kRsrcWord3);
 }
 
+// A resource for the plane at p, empty (loads return zero, stores are
+// dropped) when it is not to be touched.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_at(const char *p, long long plane_bytes, bool live = true)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p), (short)0, live ? (int)plane_bytes : 0,
+                                             kRsrcWord3);
+}
+
+// Compiles to nothing, but code after it in a branch is not turned into
+// selects: for wave-uniform branches that are rarely taken.
+__device__ __forceinline__ void keep_branch() { asm volatile(""); }
+
 // The same for a plane the stencil may reach outside the grid (z < 0 or
 // z >= nz): a ghost plane gets an empty resource, so its loads return the
 // zeros it holds without reading memory.
@@ -364,19 +376,31 @@ __device__ __forceinline__ void fold_max(const StepArgs &a, int lid, float m)
 }
 
 // Receiver epilogue: after the whole tile column is written, copy the
-// receivers this work-group owns into the trace row.
+// receivers this work-group owns (r0 .. r1 - 1 of its tables, looked up
+// before the march) into the trace row.  A thread's first table entries are
+// loaded before the wait for the column's stores, so that on small grids,
+// where a launch is a chain of memory latencies, they add none to it.
 template <int KIND>
-__device__ __forceinline__ void sample_receivers(const StepArgs &a, int lid, int tid, int nt,
-                                                 float scale)
+__device__ __forceinline__ void sample_receivers(const StepArgs &a, int r0, int r1, int tid, int nt, float scale)
 {
-    if (!a.trace_row)
-        return;
-    const int r0 = a.rec_start[lid], r1 = a.rec_start[lid + 1];
     if (r0 == r1)
         return;
+    int i = r0 + tid;
+    long long off = 0;
+    int idx = 0;
+    if (i < r1) {
+        off = a.rec_off[i];
+        idx = a.rec_idx[i];
+    }
     __syncthreads();
-    for (int i = r0 + tid; i < r1; i += nt)
-        a.trace_row[a.rec_idx[i]] = read_elem<KIND>(a.out, a.rec_off[i], scale);
+    while (i < r1) {
+        a.trace_row[idx] = read_elem<KIND>(a.out, off, scale);
+        i += nt;
+        if (i < r1) {
+            off = a.rec_off[i];
+            idx = a.rec_idx[i];
+        }
+    }
 }
 
 // Calls f(integral_constant<int, S>) for S = B, B+1, ... < E while f
@@ -463,6 +487,8 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     // reading memory.
     const bool col_interior = x < a.nx;
     const bool col_full = x + 3 < a.nx;
+    // whether this tile holds the grid's ragged last group (uniform)
+    const bool ragged = (a.nx & 3) != 0 && tx == a.ntx - 1;
 
     // own rows: byte offsets within a plane (kOff when masked)
     int row[RY];
@@ -558,6 +584,13 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     }
     const float sval = src_r >= 0 ? src_value(a) * sc.out_inv : 0.f;
 
+    // this work-group's receivers
+    int rec0 = 0, rec1 = 0;
+    if (a.trace_row) {
+        rec0 = a.rec_start[lid];
+        rec1 = a.rec_start[lid + 1];
+    }
+
     const long long pbytes = a.plane * (long long)EB;
     const __amdgpu_buffer_rsrc_t gz_r = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(a.gz), (short)0, a.nz * (int)sizeof(float), kRsrcWord3);
@@ -597,12 +630,33 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     Raw4<KIND> pv[2][RY], kv[2][RY], hv[2][HPT];
     f4 hv2[FUS ? 2 : 1][FUS ? HPT : 1];
     float gzv[2], gzq[2];  // g_z of the plane and (adjoint) of the queue plane four positions on
+    // Addresses of the planes being loaded and written.  16-bit storage
+    // advances them by one plane per iteration, two scalar adds per field in
+    // place of the multiplies of an absolute address (83 -> 54 scalar
+    // instructions a plane: 512^3 FP16 u-and-change 250 -> 244 us, 256^3 FP16
+    // 32.0 -> 30.4); the FP32 kernels, which have issue slots to spare, run
+    // 0.5-1 % faster with absolute ones (256^3 39.5 against 39.8 us).
+    constexpr bool INC = SCALED;
+    const long long zstep = down ? -pbytes : pbytes;
+    const long long zfirst = (long long)(zp(0) + kGhost) * pbytes;
+    const char *pq = reinterpret_cast<const char *>(a.cur) + zfirst + 4 * zstep;
+    const char *ph = reinterpret_cast<const char *>(a.cur) + zfirst;
+    const char *pp = reinterpret_cast<const char *>(UV ? a.dlt : a.nxt) + zfirst;
+    const char *pk = reinterpret_cast<const char *>(a.k) + zfirst;
+    const char *po = reinterpret_cast<const char *>(a.out) + zfirst;
+    const char *pd = UV ? reinterpret_cast<const char *>(a.dlt) + zfirst : nullptr;
+    const int nq = min(len, down ? z1 - 4 : a.nz - 4 - z0);  // positions whose queue plane is in the grid
+    // loads march position l, which must follow the one loaded before; past
+    // the chunk's end the last position is loaded again (and goes unused)
     auto prefetch = [&](int l, int slot, int set) {
-        const int z = zp(l), zq = zp(l + 4);
-        const __amdgpu_buffer_rsrc_t rq = stencil_plane_rsrc(a.cur, pbytes, zq, a.nz);
-        const __amdgpu_buffer_rsrc_t rp = plane_rsrc(UV ? a.dlt : a.nxt, pbytes, z);
-        const __amdgpu_buffer_rsrc_t rk = plane_rsrc(a.k, pbytes, z);
-        const __amdgpu_buffer_rsrc_t rh = plane_rsrc(a.cur, pbytes, z);
+        if constexpr (!INC)
+            l = min(l, len - 1);
+        const int z = zp(INC ? min(l, len - 1) : l);
+        const __amdgpu_buffer_rsrc_t rq =
+            INC ? rsrc_at(pq, pbytes, l < nq) : stencil_plane_rsrc(a.cur, pbytes, zp(l + 4), a.nz);
+        const __amdgpu_buffer_rsrc_t rp = INC ? rsrc_at(pp, pbytes) : plane_rsrc(UV ? a.dlt : a.nxt, pbytes, z);
+        const __amdgpu_buffer_rsrc_t rk = INC ? rsrc_at(pk, pbytes) : plane_rsrc(a.k, pbytes, z);
+        const __amdgpu_buffer_rsrc_t rh = INC ? rsrc_at(ph, pbytes) : plane_rsrc(a.cur, pbytes, z);
 #pragma unroll
         for (int r = 0; r < RY; ++r) {
             q[slot][r] = load4<KIND, PK>(rq, own_ld[r], 1.f);
@@ -613,7 +667,7 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
         for (int h = 0; h < HPT; ++h)
             hv[set][h] = load_raw4<KIND, PK>(rh, h_b[h]);
         if constexpr (FUS) {
-            const __amdgpu_buffer_rsrc_t raq = stencil_plane_rsrc(a.aux, pbytes, zq, a.nz);
+            const __amdgpu_buffer_rsrc_t raq = stencil_plane_rsrc(a.aux, pbytes, zp(l + 4), a.nz);
             const __amdgpu_buffer_rsrc_t rah = plane_rsrc(a.aux, pbytes, z);
 #pragma unroll
             for (int r = 0; r < RY; ++r)
@@ -622,9 +676,16 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
             for (int h = 0; h < HPT; ++h)
                 hv2[set][h] = load4<KIND, PK>(rah, h_b[h], 1.f);
         }
-        gzv[set] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gz_r, 4u * z, 0, 0));
+        gzv[set] = gz_at(z);
         if constexpr (ADJ)
-            gzq[set] = gz_at(zq);
+            gzq[set] = gz_at(zp(l + 4));
+        if constexpr (INC) {
+            const long long st = l + 1 < len ? zstep : 0;
+            pq += st;
+            ph += st;
+            pp += st;
+            pk += st;
+        }
     };
     prefetch(0, 8, 0);
 
@@ -637,9 +698,8 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
             if (l >= len)
                 return false;
             const int z = zp(l);
-            const int cur_set = s & 1;
-            // next plane (clamped on the last one, whose loads go unused)
-            prefetch(min(l + 1, len - 1), (s + 9) % QS, cur_set ^ 1);
+            constexpr int cur_set = s & 1;
+            prefetch(l + 1, (s + 9) % QS, cur_set ^ 1);
             // imaging modes: this plane's accumulator values, loaded before
             // the arithmetic so that their latency overlaps it.  Each cell is
             // read and written once per step, but with the z-march reversed
@@ -717,8 +777,12 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                 }
             }
 
-            const __amdgpu_buffer_rsrc_t ro = plane_rsrc(a.out, pbytes, z);
-            const __amdgpu_buffer_rsrc_t rdl = plane_rsrc(UV ? a.dlt : a.out, pbytes, z);
+            const __amdgpu_buffer_rsrc_t ro = INC ? rsrc_at(po, pbytes) : plane_rsrc(a.out, pbytes, z);
+            const __amdgpu_buffer_rsrc_t rdl = rsrc_at(UV ? pd : po, pbytes);
+            if constexpr (INC)
+                po += zstep;
+            if constexpr (UV)
+                pd += zstep;
 #pragma unroll
             for (int r = 0; r < RY; ++r) {
                 const f4 pvd = decode4<KIND>(pv[cur_set][r]);
@@ -842,11 +906,14 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                 }
                 if constexpr (FUS)
                     add_grad(img);
-                if (src_r == r && z == a.src_z) {
+                if (z == a.src_z) {
+                    keep_branch();  // one plane of the grid
+                    if (src_r == r) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (e == src_e)
-                            out.v[e] += sval;
+                        for (int e = 0; e < 4; ++e)
+                            if (e == src_e)
+                                out.v[e] += sval;
+                    }
                 }
                 f4 dn;  // d^{n+1} in its own units (u-and-change storage)
                 if constexpr (UV) {
@@ -857,7 +924,8 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                 // In a ragged last group the cells past nx are right-ghost
                 // cells, which hold zero: writing zero there keeps them so and
                 // lets the group go out as one whole store (no partial writes).
-                if (!col_full) {
+                if (ragged) {
+                    keep_branch();  // the last tile column of a grid with nx % 4 != 0
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (x + e >= a.nx) {
@@ -883,7 +951,7 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
 
     if constexpr (SCALED)
         fold_max(a, lid, tmax * sc.out);
-    sample_receivers<KIND>(a, lid, tid, NT, sc.out);
+    sample_receivers<KIND>(a, rec0, rec1, tid, NT, sc.out);
 }
 
 template <int KIND, int TXV, int TY, int RY>
