@@ -260,47 +260,67 @@ void sponge_profile(int n, int width, double alpha, std::vector<float> &g)
 //     per CU (z split into as many chunks as that takes), beat both smaller
 //     work-groups and more of them; 256 x 8 tiles edge out 128 x 16 and
 //     64 x 32 by about 1.5%;
-//   - 16-bit storage moves half the bytes per load, so a thread needs two
-//     rows to keep enough bytes in flight: 128 x 32 tiles of two rows per
-//     thread at 256 work-groups run 594 Gpts/s against 482 for 256 x 8;
-//   - u-and-change storage (five streams) does best with 128 x 16 tiles of
-//     two rows per thread at 512 work-groups (478 against 361);
+//   - 16-bit storage moves half the bytes per load, so on the largest grids
+//     a thread needs two rows to keep enough bytes in flight;
 //   - in every case the best z split fills whole rounds of the work-groups
-//     the GPU holds at once (one or two per CU here): 755 x 994 tiles of
-//     256 x 8 in one chunk are 375 work-groups, a round and a half of 256.
-// Every chunk re-reads 8 planes of u^n, so chunks are kept at >= 32 planes.
+//     the GPU holds at once: 755 x 994 tiles of 256 x 8 in one chunk are 375
+//     work-groups, a round and a half of 256.
+// Every chunk re-reads 8 planes of u^n, so FP32 chunks are kept at >= 8
+// planes (32 for a tile shape the caller chose).
 // Grids of fewer than 2^22 cells fit in the caches and are latency-bound:
 // there, about 512 work-groups with chunks down to one plane run 3-6x
 // faster per step than 32-plane chunks (48^3: 3.9 against 24.8 us per
-// step; 128^3: 9.5 against 25.9; 192^3: about 25 against 29).
+// step; 128^3: 7.3 against 25.9).
 constexpr int kAutoVariant = 10;     // t256x8_r1 (FP32)
 constexpr int kAutoNarrowVariant = 6;  // t128x16_r1 (FP32 when 256-wide tiles would idle lanes)
-constexpr int kAuto16Variant = 4;    // t128x16_r2 (FP16 / BF16, two levels)
-constexpr int kAutoUvVariant = 12;   // t128x32_r2 (u-and-change storage)
+constexpr int kAuto16Variant = 4;    // t128x16_r2 (FP16 / BF16, two levels, the largest grids)
 constexpr int kSmallVariant = 2;     // t64x16_r1 for grids of fewer than 2^22 cells
 constexpr int kTargetWorkgroupsSmall = 512;
-constexpr int kMinChunk = 32;
+constexpr int kMinChunkGiven = 32;  // tile shape chosen by the caller, and kAuto16Variant
 constexpr int kMinChunkSmall = 1;
-constexpr int kMinChunkNarrow = 8;
+constexpr int kMinChunk = 8;
 
-// Work-groups of the tiled kernel of variant v that the current GPU holds at
-// once (occupancy per CU times CUs).
+// Work-groups of variant v that fit on a CU at once (occupancy API, asked
+// once per device, storage type and variant), and the GPU's CUs.
+int fit_per_cu(int kind, int v, int *cus)
+{
+    static std::mutex mu;
+    static int known[kMaxDevices][kNumKinds][kNumVariants] = {};
+    static int known_cus[kMaxDevices] = {};
+    const Variant &V = kVariants[v];
+    const StepKernel f = V.fn[kind] ? V.fn[kind] : V.fn[WAVE_F32];
+    int dev = 0, per_cu = 0;
+    *cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess)
+        dev = -1;
+    std::lock_guard<std::mutex> lock(mu);
+    const bool keep = dev >= 0 && dev < kMaxDevices;
+    if (keep && known[dev][kind][v]) {
+        *cus = known_cus[dev];
+        return known[dev][kind][v];
+    }
+    const bool asked = dev >= 0 &&
+                       hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && *cus >= 1;
+    if (!asked)
+        *cus = 256;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, V.txv * V.ty, 0) != hipSuccess || per_cu < 1)
+        return 1;
+    if (keep && asked) {
+        known_cus[dev] = *cus;
+        known[dev][kind][v] = per_cu;
+    }
+    return per_cu;
+}
+
 // Work-groups of variant v that make one round: 8 waves (512 threads) per
 // CU, as one work-group of 512 threads or two of 256, bounded by how many
-// fit at once (occupancy API).  Two resident 512-thread work-groups per CU
-// measured slower than one: they split the CU's bandwidth and add a tail.
+// fit at once.  Two resident 512-thread work-groups per CU measured slower
+// than one: they split the CU's bandwidth and add a tail.
 long long round_workgroups(int kind, int v)
 {
-    const Variant &V = kVariants[v];
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
-    const StepKernel f = kind == WAVE_F32 || V.fn[kind] ? V.fn[kind] : V.fn[WAVE_F32];
-    const int threads = V.txv * V.ty;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    return (long long)cus * std::min(per_cu, std::max(1, 512 / threads));
+    int cus = 0;
+    const int per_cu = fit_per_cu(kind, v, &cus);
+    return (long long)cus * std::min(per_cu, std::max(1, 512 / (kVariants[v].txv * kVariants[v].ty)));
 }
 
 // z-chunk length for a grid of `tiles` x-y tiles and rounds of `cap`
@@ -352,35 +372,102 @@ double tile_fit(int nx, int ny, int tx, int tyr)
     return lanes * even;
 }
 
+// Tile shape and z-chunk of a 16-bit step on a grid of 2^22 cells or more:
+// the pair with the least
+//     T = 3 us + tau R (zc + 3) u^alpha,   R = ceil(nwg / cap), u = nwg / (R cap)
+// over the 64 x 16 tiles of one row per thread (as many work-groups as fit
+// on a CU, three of 256 threads: 12 waves) and the 128 x 32 tiles of two
+// rows (one of 512 threads, with fewer halo rows and half the loads per
+// byte).  tau is a plane's time in a full round, alpha how much of it the
+// idle CUs of a part-filled round give back (the small tiles share more of
+// it: three work-groups of a CU wait for each other's memory).  A chunk costs
+// its queue fill, about three planes' time, and rounds cost nothing beyond
+// their share, unlike the FP32 step's: these kernels are bound by issue and
+// latency rather than bandwidth.  Fitted on 39 grids of 2^22 .. 2^26 cells
+// with every tile shape and chunk count timed: the choice averages 1.015
+// times the fastest plan; one tile shape with chunks of at least 32 planes
+// averaged 1.64 (two levels) and 1.73 (u and change) times it (203x181x157
+// FP16: 38.3 -> 17.6 us a step; 320x288x272: 60.3 -> 44.6).
+struct Plan16 {
+    int v;
+    double tau, alpha;
+};
+constexpr int kPlan16Small = 2, kPlan16Large = 12;  // t64x16_r1, t128x32_r2
+constexpr Plan16 kPlan16[2][2] = {{{kPlan16Small, 1.20, 0.50}, {kPlan16Large, 1.41, 0.10}},   // two levels
+                                  {{kPlan16Small, 1.44, 0.50}, {kPlan16Large, 1.70, 0.25}}};  // u and change
+
+int plan16(int nx, int ny, int nz, int kind, int *zc)
+{
+    double best = 0.0;
+    int v = kPlan16Large;
+    *zc = nz;
+    for (const Plan16 &p : kPlan16[is_uv(kind) ? 1 : 0]) {
+        const Variant &V = kVariants[p.v];
+        const int tx = 4 * V.txv, tyr = V.ty * V.ry;
+        const long long tiles = (long long)((nx + tx - 1) / tx) * ((ny + tyr - 1) / tyr);
+        int cus = 0;
+        const int per_cu = fit_per_cu(kind, p.v, &cus);
+        const long long cap = (long long)cus * (p.v == kPlan16Large ? 1 : std::min(per_cu, 3));
+        for (int c = 1; c <= nz; ++c) {
+            const int z = (nz + c - 1) / c;
+            if (c > 1 && z == (nz + c - 2) / (c - 1))
+                continue;  // the same chunk length as c - 1
+            const long long nwg = tiles * ((nz + z - 1) / z);
+            const long long rounds = (nwg + cap - 1) / cap;
+            const double t = 3.0 + p.tau * double(rounds) * (z + 3) * std::pow(double(nwg) / double(rounds * cap), p.alpha);
+            if (best == 0.0 || t < best) {
+                best = t;
+                v = p.v;
+                *zc = z;
+            }
+        }
+    }
+    return v;
+}
+
 Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
 {
     Geo g;
     int v = variant;
-    const bool large = (long long)nx * ny * nz >= (1ll << 22);
-    // FP32 grids whose x extent leaves more than 5 % of a 256-wide tile's
-    // lanes idle ("narrow") choose between 128 x 16 and 256 x 8 tiles by
-    // fit times the chunk rule's round efficiency (128 x 16 on a tie)
-    const bool narrow = large && kind == WAVE_F32 && variant == 0 &&
-                        double(nx) / (256.0 * ((nx + 255) / 256)) < 0.95;
-    if (narrow && zchunk <= 0) {
+    int zc = zchunk;
+    const long long cells = (long long)nx * ny * nz;
+    const bool large = cells >= (1ll << 22);
+    if (v == 0 && !large) {
+        v = kSmallVariant;
+    } else if (v == 0 && kind == WAVE_F32) {
+        // FP32: 128 x 16 or 256 x 8 tiles, by fit times the chunk rule's
+        // round efficiency.  Where at least 95 % of a 256-wide tile's lanes
+        // lie in the grid the wide tiles get 2 %: on full tiles, where both
+        // shapes score the same, they are 1.5-3 % faster (512^3: 323 against
+        // 337 us; 256^3: 38.9 against 39.8).
+        v = double(nx) / (256.0 * ((nx + 255) / 256)) < 0.95 ? kAutoNarrowVariant : kAutoVariant;
         double best = -1.0;
         for (const int cand : {kAutoNarrowVariant, kAutoVariant}) {
+            if (zchunk > 0)
+                break;
             const Variant &C = kVariants[cand];
             const int tx = 4 * C.txv, tyr = C.ty * C.ry;
             const long long tiles = (long long)((nx + tx - 1) / tx) * ((ny + tyr - 1) / tyr);
             double eff = 0.0;
-            (void)fill_rounds_chunk(tiles, nz, kMinChunkNarrow, round_workgroups(kind, cand), &eff);
+            const int z = fill_rounds_chunk(tiles, nz, kMinChunk, round_workgroups(kind, cand), &eff);
             eff *= tile_fit(nx, ny, tx, tyr);
+            if (cand == kAutoVariant && double(nx) / (256.0 * ((nx + 255) / 256)) >= 0.95)
+                eff *= 1.02;
             if (eff > best * (1.0 + 1e-9)) {
                 best = eff;
                 v = cand;
+                zc = z;
             }
         }
+    } else if (v == 0) {
+        // 16-bit.  Two levels on grids of 2^27 cells or more take 128 x 16
+        // tiles of two rows in two work-groups per CU: BF16 512^3 187 us
+        // against 195 with 128 x 32 (FP16 205 against 194)
+        int z = nz;
+        v = !is_uv(kind) && cells >= (1ll << 27) ? kAuto16Variant : plan16(nx, ny, nz, kind, &z);
+        if (zc <= 0 && v != kAuto16Variant)
+            zc = z;
     }
-    if (v == 0)
-        v = !large ? kSmallVariant
-                   : kind == WAVE_F32 ? (narrow ? kAutoNarrowVariant : kAutoVariant)
-                                      : is_uv(kind) ? kAutoUvVariant : kAuto16Variant;
     g.v = v;
     if (v == kNaive) {
         g.ntx = g.nty = g.nchunks = 0;
@@ -394,14 +481,12 @@ Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
     g.ntx = (nx + tx - 1) / tx;
     g.nty = (ny + tyr - 1) / tyr;
     const long long tiles = (long long)g.ntx * g.nty;
-    int zc = zchunk;
     if (zc <= 0 && !large) {
         const long long chunks = std::max(1ll, (kTargetWorkgroupsSmall + tiles / 2) / tiles);
         zc = std::max(int((nz + chunks - 1) / chunks), std::min(kMinChunkSmall, nz));
     } else if (zc <= 0) {
-        // large grids: whole rounds, chunks of at least 32 planes (8 for
-        // the narrow-grid tiles, whose tiles are few)
-        zc = fill_rounds_chunk(tiles, nz, narrow ? kMinChunkNarrow : kMinChunk, round_workgroups(kind, v));
+        // a tile shape chosen by the caller, or the largest two-level grids
+        zc = fill_rounds_chunk(tiles, nz, kMinChunkGiven, round_workgroups(kind, v));
     }
     if (zc > nz)
         zc = nz;
