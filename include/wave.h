@@ -221,9 +221,10 @@ int wave_sync(wave_ctx *ctx);
  * a^0 and a^{-1} the fields the run started from, R^T adding each
  * receiver's value at its cell).  On the device the adjoint field is kept
  * as phi = k lambda, so that the adjoint step is the forward stencil update
- * applied to G phi; every forward level a^{m-1} is recomputed segment by
- * segment from checkpoints (a^{c-1}, a^c) taken every C steps, and the sum
- * is accumulated in FP64.  wave_adjoint_velocity returns dJ/dv = 2 v dt^2
+ * applied to G phi.  The forward run stores the Laplacians lap(a^{m-1}) it
+ * computes anyway, those of earlier segments being recomputed from
+ * checkpoints (a^{c-1}, a^c) taken every C steps, and the sum is accumulated
+ * in FP64.  wave_adjoint_velocity returns dJ/dv = 2 v dt^2
  * dJ/dk instead.
  */
 
@@ -231,10 +232,12 @@ int wave_sync(wave_ctx *ctx);
  * traces, fields and step counter afterwards), and keep what the adjoint
  * run needs: checkpoints every `every` steps (0: the library picks the
  * largest segment that fits in half of the free device memory -- all levels
- * of the run when they fit, so that nothing is recomputed) and the levels
- * of the last segment.  src_dev: nt FP32 device values (copied; NULL = no
- * source).  Library-owned device memory: (2 ceil(nt / C) + C) field levels
- * of wave_layout bytes each, kept until the next call or wave_destroy.
+ * of the run when they fit, so that nothing is recomputed) and the
+ * Laplacians of the last segment's levels.  src_dev: nt FP32 device values
+ * (copied; NULL = no source).  Library-owned device memory, kept until the
+ * next call or wave_destroy: 2 ceil(nt / C) fields of wave_layout bytes each
+ * (none when C >= nt) and C Laplacians of the interior cells, rows padded to
+ * a multiple of 128 bytes.
  * WAVE_ENOMEM when it cannot be allocated, WAVE_EINVAL for 16-bit storage. */
 int wave_forward_checkpointed(wave_ctx *ctx, int32_t nt, const float *src_dev, int32_t every);
 
@@ -245,8 +248,9 @@ int wave_forward_checkpointed(wave_ctx *ctx, int32_t nt, const float *src_dev, i
  *                   receives dJ/dk, or has it added when accumulate != 0.
  * Receivers sharing a cell contribute the sum of their derivatives.  May be
  * called again for another trace_grad of the same run (levels are then
- * recomputed).  Library-owned device memory: two FP32 fields and one FP64
- * field of the layout, kept until wave_destroy.  The context's fields,
+ * recomputed).  Library-owned device memory: two FP32 fields of the layout
+ * and one FP64 value per interior cell (rows padded as above), kept until
+ * wave_destroy.  The context's fields,
  * traces and step counter are left as the forward run left them. */
 int wave_adjoint(wave_ctx *ctx, const float *trace_grad_dev, double *grad_dev, int32_t accumulate);
 
@@ -277,13 +281,14 @@ int wave_adjoint_velocity(wave_ctx *ctx, const float *trace_grad_dev, const floa
  * fails. */
 int wave_velocity_to_k(const float *v_dev, int64_t n, double dt, float *k_dev, void *stream);
 
-/* The adjoint run normally makes phi^{m-1} and adds the imaging term of
- * phi^m in one pass over the grid (36 instead of 44 bytes per cell and
- * step); on = 0 selects two separate passes.  Both give the same result
- * bit for bit; the switch exists for that cross-check. */
+/* The adjoint run normally adds the imaging terms of phi^{m+1} and phi^m
+ * in the pass that makes phi^{m-1} from them, every other step (16 and 40
+ * bytes per cell in turn); on = 0 selects separate passes of one term each.
+ * Both give the same result bit for bit; the switch exists for that
+ * cross-check. */
 int wave_set_adjoint_fusion(wave_ctx *ctx, int32_t on);
 
-/* Steps, segment length, segments and bytes of checkpoint/level storage of
+/* Steps, segment length, segments and bytes of checkpoint/Laplacian storage of
  * the last checkpointed forward run (nt = 0 when there is none). */
 int wave_grad_info(const wave_ctx *ctx, int32_t *nt, int32_t *every, int32_t *segments, int64_t *bytes);
 

@@ -1,5 +1,5 @@
-// Fused adjoint step + imaging term of the gradient run (FP32), one per tile
-// shape.
+// Fused adjoint step + imaging terms of the gradient run (FP32), one per
+// tile shape.
 #include "wave_step.h"
 
 namespace wavek {

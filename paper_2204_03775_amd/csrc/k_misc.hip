@@ -8,31 +8,57 @@ namespace wavek {
 
 // Adds k * trace_grad[row][r] at the receiver cells: one thread per distinct
 // cell, summing its receivers in a fixed order (deterministic, no atomics).
-// With s_val set, the source value of the forward step that made this level
-// is k at the source cell times a fixed wavelet value, so its derivative
-// with respect to that k adds lambda s / k = phi s / k^2 there (lambda =
-// phi / k): thread src_thread takes it -- the thread of the receiver cell
-// that is also the source cell (after its own add), or thread ncells.
+// Only phi^nt needs it; the adjoint steps add their own level's.
 __global__ void inject_receivers(float *phi, const float *__restrict__ k, const long long *__restrict__ cell_off,
                                  const int *__restrict__ cell_start, const int *__restrict__ cell_rec,
-                                 int ncells, const float *__restrict__ tg_row, const float *__restrict__ s_val,
-                                 long long src_off, int src_thread, double *acc)
+                                 int ncells, const float *__restrict__ tg_row)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    float v = 0.f;
-    if (c < ncells) {
-        float s = 0.f;
-        for (int i = cell_start[c]; i < cell_start[c + 1]; ++i)
-            s += tg_row[cell_rec[i]];
-        const long long o = cell_off[c];
-        v = fmaf(k[o], s, phi[o]);
-        phi[o] = v;
-    } else if (c == ncells && s_val) {
-        v = phi[src_off];
-    }
-    if (s_val && c == src_thread) {
-        const double kk = k[src_off];
-        acc[src_off] += (double)v * (double)*s_val / (kk * kk);
+    if (c >= ncells)
+        return;
+    float s = 0.f;
+    for (int i = cell_start[c]; i < cell_start[c + 1]; ++i)
+        s += tg_row[cell_rec[i]];
+    const long long o = cell_off[c];
+    phi[o] = fmaf(k[o], s, phi[o]);
+}
+
+// The source value of the forward step that made this level is k at the
+// source cell times a fixed wavelet value, so its derivative with respect to
+// that k adds lambda s / k = phi s / k^2 there (lambda = phi / k); one
+// thread, summed apart from the imaging terms.
+__global__ void source_term(const float *phi, const float *k, long long off, const float *s, double *sum)
+{
+    const double kk = k[off];
+    *sum += (double)phi[off] * (double)*s / (kk * kk);
+}
+
+// Imaging terms of one or two adjoint levels as a pass of their own: sum (+)=
+// (G phi_b / k) lap_b, then + (G phi_a / k) lap_a (the older level b first;
+// phi_b may be NULL).  Rows of four-cell groups: one thread per group.
+__global__ __launch_bounds__(256) void imaging_terms(const float *__restrict__ phi_a, const float *__restrict__ lap_a,
+                                                     const float *__restrict__ phi_b, const float *__restrict__ lap_b,
+                                                     const float *__restrict__ k, const float *__restrict__ gx,
+                                                     const float *__restrict__ gy, const float *__restrict__ gz,
+                                                     int nx, int ny, int nz, int px, int x0, long long plane,
+                                                     int lpx, long long lplane, int first, double *sum)
+{
+    const int nxq = (nx + 3) / 4;
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= ny * nxq)
+        return;
+    const int y = q / nxq, x = 4 * (q - y * nxq);
+    for (int z = blockIdx.z; z < nz; z += gridDim.z) {
+        const long long f = (long long)(z + kGhost) * plane + (long long)(y + kGhost) * px + x0 + x;
+        const long long l = z * lplane + (long long)y * lpx + x;
+        for (int e = 0; e < 4 && x + e < nx; ++e) {
+            const float g = gx[x + e] * gy[y] * gz[z];
+            double t = first ? 0.0 : sum[l + e];
+            if (phi_b)
+                t += (double)((g * phi_b[f + e]) / k[f + e] * lap_b[l + e]);
+            t += (double)((g * phi_a[f + e]) / k[f + e] * lap_a[l + e]);
+            sum[l + e] = t;
+        }
     }
 }
 
@@ -74,24 +100,27 @@ __global__ __launch_bounds__(1024) void misfit_kernel(const float *__restrict__ 
         *out = 0.5 * part[0];
 }
 
-// dense[z][y][x] (+)= acc at the interior cells of the field layout; with
-// v set, the chain rule to velocity: dJ/dv = dJ/dk * 2 dt^2 v (k = (v dt)^2).
-__global__ __launch_bounds__(256) void grad_to_dense(const double *__restrict__ acc, double *dense, int nx,
-                                                    int ny, int nz, int px, int x0, long long plane,
-                                                    int accumulate, const float *__restrict__ v,
-                                                    double two_dt2)
+// dense[z][y][x] (+)= sum; the source cell (src, or -1) also gets *src_sum.
+// With v set, the chain rule to velocity: dJ/dv = dJ/dk * 2 dt^2 v
+// (k = (v dt)^2).  Blocks along rows: no division by the grid's sizes.
+__global__ __launch_bounds__(256) void grad_to_dense(const double *__restrict__ sum, double *dense, int nx,
+                                                    int ny, int nz, int lpx, long long lplane, int accumulate,
+                                                    const float *__restrict__ v, double two_dt2, long long src,
+                                                    const double *__restrict__ src_sum)
 {
-    const long long n = (long long)nx * ny * nz;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(i % nx);
-        const int y = (int)((i / nx) % ny);
-        const int z = (int)(i / ((long long)nx * ny));
-        double g = acc[(long long)(z + kGhost) * plane + (long long)(y + kGhost) * px + x0 + x];
-        if (v)
-            g *= two_dt2 * (double)v[i];
-        dense[i] = accumulate ? dense[i] + g : g;
-    }
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= nx)
+        return;
+    for (int z = blockIdx.z; z < nz; z += gridDim.z)
+        for (int y = blockIdx.y; y < ny; y += gridDim.y) {
+            const long long i = ((long long)z * ny + y) * nx + x;
+            double g = sum[z * lplane + (long long)y * lpx + x];
+            if (i == src)
+                g += *src_sum;
+            if (v)
+                g *= two_dt2 * (double)v[i];
+            dense[i] = accumulate ? dense[i] + g : g;
+        }
 }
 
 // Clears both ticket sets at the start of a batched run (a kernel rather

@@ -76,7 +76,8 @@ struct Variant {
     StepKernel fn[kNumKinds];  // by storage type; all NULL for "auto" and "naive"
     BatchKernel batch[3];      // FP32, FP16, BF16 (two-level storage)
     RunKernel run[3];          // the same, every step of a run in one launch
-    StepKernel adj[3];  // adjoint step, imaging step, fused adjoint + imaging (FP32)
+    StepKernel adj[2];  // adjoint step, adjoint step + imaging terms (FP32)
+    StepKernel lap[2];  // FP32 step that stores the Laplacian: streaming, cache-resident loads
     FlowKernel flow;    // data-flow batched step (FP32)
     StepKernel fwd_cached;  // FP32 step with cache-resident load policies
     int txv, ty, ry;
@@ -90,14 +91,15 @@ struct Variant {
      step_batch<WAVE_BF16, TXV, TY, RY>},                                                         \
     {step_batch_run<WAVE_F32, TXV, TY, RY>, step_batch_run<WAVE_F16, TXV, TY, RY>,                \
      step_batch_run<WAVE_BF16, TXV, TY, RY>},                                                     \
-    {adjoint_tiled<kAdj, TXV, TY, RY>, adjoint_tiled<kImg, TXV, TY, RY>, adjoint_tiled<kFus, TXV, TY, RY>}, \
+    {adjoint_tiled<kAdj, TXV, TY, RY>, adjoint_tiled<kFus, TXV, TY, RY>},                         \
+    {step_tiled_lap<false, TXV, TY, RY>, step_tiled_lap<true, TXV, TY, RY>},                      \
     step_flow<TXV, TY, RY>, step_tiled_cached<TXV, TY, RY>
 
 const Variant kVariants[] = {
     {"auto", {nullptr, nullptr, nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr},
-     {nullptr, nullptr, nullptr}, nullptr, nullptr, 0, 0, 0},
+     {nullptr, nullptr}, {nullptr, nullptr}, nullptr, nullptr, 0, 0, 0},
     {"naive", {nullptr, nullptr, nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr},
-     {nullptr, nullptr, nullptr}, nullptr, nullptr, 0, 0, 0},
+     {nullptr, nullptr}, {nullptr, nullptr}, nullptr, nullptr, 0, 0, 0},
     {"t64x16_r1", TILED(16, 16, 1), 16, 16, 1},
     {"t128x8_r1", TILED(32, 8, 1), 32, 8, 1},
     {"t128x16_r2", TILED(32, 8, 2), 32, 8, 2},
@@ -147,32 +149,39 @@ struct Geo {
 constexpr int kRingInts = kMaxStride + 4 * kMaxSlots * kMaxStride;
 
 // State of the gradient computation (FP32 storage): the checkpoints and the
-// level store of the last checkpointed forward run, the adjoint fields and
-// the FP64 accumulator, all in the field layout (ghost cells zero).
+// store of the last checkpointed forward run and the adjoint fields, in the
+// field layout (ghost cells zero), and the Laplacians and the FP64 sum, which
+// hold interior cells only.
 struct wave_grad_state {
     int64_t step0 = 0;  // step counter at the start of the forward run
     int nt = 0;         // steps of the run (0: no run recorded)
     int every = 0;      // segment length C
     int nseg = 0;       // segments: segment i covers steps i*C .. min((i+1)*C, nt) - 1
-    int held = -1;      // segment whose levels c+1 .. the store holds
+    int held = -1;      // segment whose levels' Laplacians the store holds
     bool has_src = false;
-    void *slab = nullptr;  // 2 * nseg checkpoint levels, then C store levels
-    size_t slab_levels = 0;
+    // checkpoints (two fields each; none with a single segment, which is
+    // never recomputed), then the store: lap a^c .. lap a^{c+C-1} of a segment
+    void *slab = nullptr;
+    size_t slab_bytes = 0;
     float *src = nullptr;  // the run's source values [nt]
     int src_cap = 0;
     void *phi[2] = {nullptr, nullptr};
-    double *acc = nullptr;
-    // receiver cells (distinct) and, per cell, its receivers
+    double *acc = nullptr;      // FP64 sum, then one more value: the source term
+    // receiver cells (distinct) by work-group of the adjoint's tiling, and,
+    // per cell, its receivers
+    int *cell_wg = nullptr;
     long long *cell_off = nullptr;
     int *cell_start = nullptr, *cell_rec = nullptr;
     int ncells = -1;
-    std::vector<long long> cell_off_host;  // the cells' offsets, host copy
+    int cell_v = -1, cell_zc = -1;  // the tiling of cell_wg
 };
 
 struct wave_ctx {
     wave_params_t p;
     wave_layout_t lay;    // layout of the u fields (and of the stored k)
     wave_layout_t lay32;  // FP32 layout (the caller's k for 16-bit storage)
+    int lap_px = 0;           // row pitch and plane of the gradient's Laplacians and sum
+    long long lap_plane = 0;
     int device = 0;
     hipStream_t stream = nullptr;
     const void *k = nullptr;  // stored k: the caller's (FP32) or k16
@@ -594,17 +603,22 @@ StepArgs make_args(const wave_ctx *c)
     a.exps = c->ring;
     a.maxes = reinterpret_cast<unsigned *>(c->ring + kMaxStride);
     a.out = c->prev;
-    a.grad = nullptr;
-    a.aux = nullptr;
     a.dlt = c->dbuf;
+    a.aux = nullptr;
+    a.grad = nullptr;
+    a.lpx = c->lap_px;
+    a.first = 0;
+    a.lplane = c->lap_plane;
+    a.inj_rec = nullptr;
     a.zdown = 0;
     return a;
 }
 
 // One forward step from (cur = u^n, prev = u^{n-1}) into `out` (== prev for
-// the in-place step), step counter and trace row as given.
+// the in-place step), step counter and trace row as given; lap u^n goes to
+// `lap` if set (FP32).
 int enqueue_forward(wave_ctx *c, void *cur, void *prev, void *out, const float *src_ptr, float src_val,
-                    int64_t step, float *trace_row)
+                    int64_t step, float *trace_row, void *lap = nullptr)
 {
     StepArgs a = make_args(c);
     a.cur = cur;
@@ -615,6 +629,8 @@ int enqueue_forward(wave_ctx *c, void *cur, void *prev, void *out, const float *
     a.step = int(step & 0x3fffffff);
     a.trace_row = trace_row;
     a.zdown = int(c->zflip++ & 1u);
+    if (lap)
+        a.dlt = lap;
 
     const int kind = c->p.dtype;
     if (c->v_used == kNaive) {
@@ -638,7 +654,8 @@ int enqueue_forward(wave_ctx *c, void *cur, void *prev, void *out, const float *
         }
     } else {
         const Variant &V = kVariants[c->v_used];
-        const StepKernel fn = (c->cache_resident && V.fwd_cached) ? V.fwd_cached : V.fn[kind];
+        const StepKernel fn = lap ? V.lap[c->cache_resident ? 1 : 0]
+                                  : (c->cache_resident && V.fwd_cached) ? V.fwd_cached : V.fn[kind];
         hipLaunchKernelGGL(fn, dim3(c->grid), dim3(V.txv * V.ty), 0, c->stream, a);
     }
     hipError_t e = hipGetLastError();
@@ -652,10 +669,10 @@ float *trace_row_of(const wave_ctx *c, int64_t step)
     return (c->traces && c->nrec > 0) ? c->traces + (size_t)step * c->nrec : nullptr;
 }
 
-int launch_step(wave_ctx *c, const float *src_ptr, float src_val)
+int launch_step(wave_ctx *c, const float *src_ptr, float src_val, void *lap = nullptr)
 {
     const int rc = enqueue_forward(c, c->cur, c->prev, c->prev, src_ptr, src_val, c->step,
-                                   trace_row_of(c, c->step));
+                                   trace_row_of(c, c->step), lap);
     if (rc != WAVE_OK)
         return rc;
     // u^{n+1} now lives in the old u^{n-1} buffer
@@ -681,6 +698,7 @@ void free_grad(wave_grad_state &g)
     free_dev(g.phi[0]);
     free_dev(g.phi[1]);
     free_dev(g.acc);
+    free_dev(g.cell_wg);
     free_dev(g.cell_off);
     free_dev(g.cell_start);
     free_dev(g.cell_rec);
@@ -775,15 +793,22 @@ Geo adjoint_geo(const wave_ctx *c)
                     0);
 }
 
-int enqueue_adjoint(wave_ctx *c, const Geo &geo, int mode, const void *cur, void *nxt, void *out,
-                    double *acc, const void *aux = nullptr)
+// One adjoint step: phi^{m-1} over `far` (phi^{m+1}) from `near` (phi^m) and
+// it, with row m-2 of tg (tg_row, NULL without receivers) added; with lap set
+// (of the level `near` images), its imaging term, and that of `far` if
+// lap_far is set too, go into the FP64 sum.
+int enqueue_adjoint(wave_ctx *c, const Geo &geo, const void *near, void *far, const float *tg_row,
+                    const void *lap = nullptr, void *lap_far = nullptr, bool first = false)
 {
+    wave_grad_state &g = c->g;
     StepArgs a = make_args(c);
-    a.cur = cur;
-    a.nxt = nxt;
-    a.out = out;
-    a.grad = acc;
-    a.aux = aux;
+    a.cur = near;
+    a.nxt = far;
+    a.out = far;
+    a.grad = g.acc;
+    a.aux = lap;
+    a.dlt = lap_far;
+    a.first = first ? 1 : 0;
     a.ntx = geo.ntx;
     a.nty = geo.nty;
     a.nchunks = geo.nchunks;
@@ -791,95 +816,151 @@ int enqueue_adjoint(wave_ctx *c, const Geo &geo, int mode, const void *cur, void
     a.nwg = geo.nwg;
     a.src_z = a.src_y = a.src_x = -1;
     a.src_ptr = nullptr;
-    a.trace_row = nullptr;
+    // the receiver cells take the receivers' place in the tables
+    a.trace_row = g.ncells > 0 ? const_cast<float *>(tg_row) : nullptr;
+    a.rec_start = g.cell_wg;
+    a.rec_off = g.cell_off;
+    a.rec_idx = g.cell_start;
+    a.inj_rec = g.cell_rec;
     a.zdown = int(c->zflip++ & 1u);
     const Variant &V = kVariants[geo.v];
-    hipLaunchKernelGGL(V.adj[mode - 1], dim3(geo.grid), dim3(V.txv * V.ty), 0, c->stream, a);
+    hipLaunchKernelGGL(V.adj[lap ? 1 : 0], dim3(geo.grid), dim3(V.txv * V.ty), 0, c->stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail(c, WAVE_EHIP, "adjoint launch failed: %s", hipGetErrorString(e));
     return WAVE_OK;
 }
 
-size_t level_bytes(const wave_ctx *c) { return (size_t)c->lay.bytes; }
-
-// Level l of segment `seg`: a^{c-1} and a^c from the checkpoint, a^{c+1} ..
-// a^{c+C} from the store (c = seg * C).
-void *level_ptr(wave_ctx *c, int seg, int64_t l)
+// The imaging terms of phi_a and (if lap_b is set) phi_b as a pass of their own.
+int enqueue_imaging(wave_ctx *c, const void *phi_a, const void *lap_a, const void *phi_b, const void *lap_b, bool first)
 {
-    wave_grad_state &g = c->g;
-    const int64_t c0 = (int64_t)seg * g.every;
-    char *base = static_cast<char *>(g.slab);
-    const size_t lb = level_bytes(c);
-    if (l <= c0)
-        return base + lb * (size_t)(2 * seg + (l == c0 ? 1 : 0));
-    return base + lb * (size_t)(2 * g.nseg + (l - c0 - 1));
+    const int groups = c->p.ny * ((c->p.nx + 3) / 4);
+    hipLaunchKernelGGL(imaging_terms, dim3((groups + 255) / 256, 1, std::min(c->p.nz, 65535)), dim3(256), 0, c->stream,
+                       (const float *)phi_a, (const float *)lap_a, (const float *)(lap_b ? phi_b : nullptr),
+                       (const float *)lap_b, (const float *)c->k, c->gx, c->gy, c->gz, c->p.nx, c->p.ny, c->p.nz,
+                       int(c->lay.pitch_x), int(c->lay.x_offset), (long long)c->lay.plane, c->lap_px, c->lap_plane,
+                       first ? 1 : 0, c->g.acc);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return fail(c, WAVE_EHIP, "imaging launch failed: %s", hipGetErrorString(e));
+    return WAVE_OK;
 }
 
-// Out-of-place forward steps of segment `seg` from its checkpoint, writing
-// levels c+1 .. c+count into the store; traces are written when `record`.
-int forward_segment(wave_ctx *c, int seg, int count, bool record)
+size_t level_bytes(const wave_ctx *c) { return (size_t)c->lay.bytes; }
+
+size_t lap_bytes(const wave_ctx *c) { return (size_t)c->lap_plane * c->p.nz * sizeof(float); }
+
+size_t checkpoints(int nseg) { return nseg > 1 ? 2 * (size_t)nseg : 0; }
+
+// Checkpoint of segment `seg` (c = seg * C): a^{c-1} (which = 0) or a^c (1).
+void *checkpoint_ptr(wave_ctx *c, int seg, int which)
+{
+    return static_cast<char *>(c->g.slab) + level_bytes(c) * (2 * (size_t)seg + which);
+}
+
+// The store's entry for the Laplacian of level l of segment `seg`.
+void *lap_ptr(wave_ctx *c, int seg, int64_t l)
+{
+    wave_grad_state &g = c->g;
+    return static_cast<char *>(g.slab) + level_bytes(c) * checkpoints(g.nseg) +
+           lap_bytes(c) * (size_t)(l - (int64_t)seg * g.every);
+}
+
+// Fill the store with the Laplacians of segment `seg` by stepping again from
+// its checkpoint.  The steps run in the two fields at `work`, which end up
+// with the segment's last two levels: the next segment's checkpoint, which
+// is just what they held before, or any two fields for the last segment.
+int recompute_segment(wave_ctx *c, int seg, void *const work[2])
 {
     wave_grad_state &g = c->g;
     const int64_t c0 = (int64_t)seg * g.every;
-    for (int j = 0; j < count; ++j) {
+    const int len = int(std::min<int64_t>(g.every, g.nt - c0));
+    void *prev = checkpoint_ptr(c, seg, 0), *cur = checkpoint_ptr(c, seg, 1);
+    for (int j = 0; j < len; ++j) {
         const int64_t n = c0 + j;  // this step writes a^{n+1}
-        const float *sp = g.has_src ? g.src + n : nullptr;
-        const int rc = enqueue_forward(c, level_ptr(c, seg, n), level_ptr(c, seg, n - 1),
-                                       level_ptr(c, seg, n + 1), sp, 0.f, g.step0 + n,
-                                       record ? trace_row_of(c, g.step0 + n) : nullptr);
+        void *out = work[(len - 1 - j) & 1 ? 0 : 1];
+        const int rc = enqueue_forward(c, cur, prev, out, g.has_src ? g.src + n : nullptr, 0.f, g.step0 + n, nullptr,
+                                       lap_ptr(c, seg, n));
         if (rc != WAVE_OK)
             return rc;
+        prev = cur;
+        cur = out;
     }
     g.held = seg;
     return WAVE_OK;
 }
 
-// Distinct receiver cells with their receivers (the adjoint source adds the
-// trace derivatives of every receiver at a cell).
-int build_receiver_cells(wave_ctx *c)
+// Distinct receiver cells, by work-group of the adjoint's tiling, with their
+// receivers (the adjoint source adds the trace derivatives of every receiver
+// at a cell).
+int build_receiver_cells(wave_ctx *c, const Geo &geo)
 {
     wave_grad_state &g = c->g;
-    if (g.ncells >= 0)
+    if (g.ncells >= 0 && g.cell_v == geo.v && g.cell_zc == geo.zc)
         return WAVE_OK;
-    std::vector<std::pair<long long, int>> r(c->nrec);
-    for (int i = 0; i < c->nrec; ++i)
-        r[i] = {elem_offset(c->lay, c->rec[3 * i], c->rec[3 * i + 1], c->rec[3 * i + 2]), i};
+    g.ncells = -1;
+    free_dev(g.cell_wg);
+    free_dev(g.cell_off);
+    free_dev(g.cell_start);
+    free_dev(g.cell_rec);
+    const Variant &V = kVariants[geo.v];
+    const int tx = 4 * V.txv, tyr = V.ty * V.ry;
+    struct Rec {
+        int wg;
+        long long off;
+        int idx;
+        bool operator<(const Rec &o) const
+        {
+            return wg != o.wg ? wg < o.wg : off != o.off ? off < o.off : idx < o.idx;
+        }
+    };
+    std::vector<Rec> r(c->nrec);
+    for (int i = 0; i < c->nrec; ++i) {
+        const int z = c->rec[3 * i], y = c->rec[3 * i + 1], x = c->rec[3 * i + 2];
+        r[i] = {((z / geo.zc) * geo.nty + y / tyr) * geo.ntx + x / tx, elem_offset(c->lay, z, y, x), i};
+    }
     std::sort(r.begin(), r.end());
     std::vector<long long> off;
-    std::vector<int> start, idx;
+    std::vector<int> start, idx, wg(geo.nwg + 1, 0);
     for (int i = 0; i < c->nrec; ++i) {
-        if (i == 0 || r[i].first != r[i - 1].first) {
-            off.push_back(r[i].first);
+        if (i == 0 || r[i].off != r[i - 1].off) {
+            off.push_back(r[i].off);
             start.push_back(i);
+            wg[r[i].wg + 1]++;
         }
-        idx.push_back(r[i].second);
+        idx.push_back(r[i].idx);
     }
     start.push_back(c->nrec);
-    g.ncells = int(off.size());
-    g.cell_off_host = off;
+    for (int i = 0; i < geo.nwg; ++i)
+        wg[i + 1] += wg[i];
+    const int ncells = int(off.size());
     off.resize(std::max<size_t>(off.size(), 1));
     idx.resize(std::max<size_t>(idx.size(), 1));
+    HIP_TRY(c, hipMalloc(&g.cell_wg, sizeof(int) * wg.size()));
     HIP_TRY(c, hipMalloc(&g.cell_off, sizeof(long long) * off.size()));
     HIP_TRY(c, hipMalloc(&g.cell_start, sizeof(int) * start.size()));
     HIP_TRY(c, hipMalloc(&g.cell_rec, sizeof(int) * idx.size()));
+    HIP_TRY(c, hipMemcpy(g.cell_wg, wg.data(), sizeof(int) * wg.size(), hipMemcpyHostToDevice));
     HIP_TRY(c, hipMemcpy(g.cell_off, off.data(), sizeof(long long) * off.size(), hipMemcpyHostToDevice));
     HIP_TRY(c, hipMemcpy(g.cell_start, start.data(), sizeof(int) * start.size(), hipMemcpyHostToDevice));
     HIP_TRY(c, hipMemcpy(g.cell_rec, idx.data(), sizeof(int) * idx.size(), hipMemcpyHostToDevice));
+    g.ncells = ncells;
+    g.cell_v = geo.v;
+    g.cell_zc = geo.zc;
     return WAVE_OK;
 }
 
 // Segment length when the caller leaves it to the library: every level of
 // the run when that fits in half of the free device memory, else the
-// largest C whose checkpoints and store (2 ceil(nt / C) + C levels) fit.
+// largest C whose checkpoints and store fit.
 int auto_segment(const wave_ctx *c, int nt)
 {
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess)
         return -1;
-    const double budget = 0.5 * double(free_b) / double(level_bytes(c));
     for (int C = nt; C >= 1; --C)
-        if (2.0 * ((nt + C - 1) / C) + C <= budget)
+        if (double(checkpoints((nt + C - 1) / C)) * double(level_bytes(c)) + double(C) * double(lap_bytes(c)) <=
+            0.5 * double(free_b))
             return C;
     return -1;
 }
@@ -1389,6 +1470,8 @@ int wave_init(wave_ctx **out, const wave_params_t *p, const void *k, void *u_cur
     c->p = *p;
     c->lay = lay;
     c->lay32 = lay32;
+    c->lap_px = int(round_up(p->nx, kRowAlignBytes / 4));
+    c->lap_plane = (long long)c->lap_px * p->ny;
     c->cache_resident = p->dtype == WAVE_F32 && fits_in_cache(p->nx, p->ny, p->nz);
     c->stream = static_cast<hipStream_t>(stream);
     c->k = k;
@@ -1729,19 +1812,18 @@ int wave_forward_checkpointed(wave_ctx *ctx, int32_t nt, const float *src_dev, i
         return fail(ctx, WAVE_ENOMEM, "not enough device memory for the checkpoints of %d steps", nt);
     wave_grad_state &g = ctx->g;
     const int nseg = (nt + C - 1) / C;
-    const size_t levels = 2 * (size_t)nseg + (size_t)C;
+    const size_t lb = level_bytes(ctx);
+    const size_t need = checkpoints(nseg) * lb + (size_t)C * lap_bytes(ctx);
     g.nt = 0;  // invalid until the run is enqueued
-    if (levels > g.slab_levels) {
+    if (need > g.slab_bytes) {
         free_dev(g.slab);
-        g.slab_levels = 0;
-        if (hipMalloc(&g.slab, levels * level_bytes(ctx)) != hipSuccess) {
+        g.slab_bytes = 0;
+        if (hipMalloc(&g.slab, need) != hipSuccess) {
             (void)hipGetLastError();
-            return fail(ctx, WAVE_ENOMEM, "cannot allocate %zu field levels (%.2f GB)", levels,
-                        levels * double(level_bytes(ctx)) / 1e9);
+            return fail(ctx, WAVE_ENOMEM, "cannot allocate the checkpoints and levels of %d steps (%.2f GB)", nt,
+                        double(need) / 1e9);
         }
-        g.slab_levels = levels;
-        // ghost cells stay zero: steps write interior cells only
-        HIP_TRY(ctx, hipMemsetAsync(g.slab, 0, levels * level_bytes(ctx), ctx->stream));
+        g.slab_bytes = need;
     }
     if (src_dev) {
         if (nt > g.src_cap) {
@@ -1759,32 +1841,26 @@ int wave_forward_checkpointed(wave_ctx *ctx, int32_t nt, const float *src_dev, i
     g.nseg = nseg;
     g.held = -1;
 
-    const size_t lb = level_bytes(ctx);
     for (int seg = 0; seg < nseg; ++seg) {
         const int64_t c0 = (int64_t)seg * C;
         const int len = int(std::min<int64_t>(C, nt - c0));
-        HIP_TRY(ctx, hipMemcpyAsync(level_ptr(ctx, seg, c0 - 1), ctx->prev, lb, hipMemcpyDeviceToDevice,
-                                    ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(level_ptr(ctx, seg, c0), ctx->cur, lb, hipMemcpyDeviceToDevice,
-                                    ctx->stream));
-        if (seg + 1 < nseg) {
-            for (int j = 0; j < len; ++j) {
-                rc = launch_step(ctx, g.has_src ? g.src + c0 + j : nullptr, 0.f);
-                if (rc != WAVE_OK)
-                    return rc;
-            }
-        } else {
-            // the last segment keeps its levels for the adjoint run
-            rc = forward_segment(ctx, seg, len, true);
+        if (nseg > 1) {
+            // whole fields, so that the copies' ghost cells are zero too
+            HIP_TRY(ctx, hipMemcpyAsync(checkpoint_ptr(ctx, seg, 0), ctx->prev, lb, hipMemcpyDeviceToDevice,
+                                        ctx->stream));
+            HIP_TRY(ctx, hipMemcpyAsync(checkpoint_ptr(ctx, seg, 1), ctx->cur, lb, hipMemcpyDeviceToDevice,
+                                        ctx->stream));
+        }
+        // the last segment's Laplacians are kept for the adjoint run
+        const bool last = seg + 1 == nseg;
+        for (int j = 0; j < len; ++j) {
+            rc = launch_step(ctx, g.has_src ? g.src + c0 + j : nullptr, 0.f,
+                             last ? lap_ptr(ctx, seg, c0 + j) : nullptr);
             if (rc != WAVE_OK)
                 return rc;
-            HIP_TRY(ctx, hipMemcpyAsync(ctx->prev, level_ptr(ctx, seg, c0 + len - 1), lb,
-                                        hipMemcpyDeviceToDevice, ctx->stream));
-            HIP_TRY(ctx, hipMemcpyAsync(ctx->cur, level_ptr(ctx, seg, c0 + len), lb,
-                                        hipMemcpyDeviceToDevice, ctx->stream));
-            ctx->step += len;
         }
     }
+    g.held = nseg - 1;
     g.nt = nt;
     return WAVE_OK;
 }
@@ -1792,119 +1868,119 @@ int wave_forward_checkpointed(wave_ctx *ctx, int32_t nt, const float *src_dev, i
 namespace {
 
 // The adjoint run of the last checkpointed forward run, leaving dJ/dk in the
-// FP64 accumulator g.acc (field layout).  With src_term, the source values
-// are taken to scale with k at the source cell, and their derivative is
-// added there.
+// FP64 sum g.acc.  With src_term, the source values are taken to scale with
+// k at the source cell, and their derivative is summed behind it.
 int adjoint_run(wave_ctx *ctx, const float *trace_grad_dev, bool src_term)
 {
     wave_grad_state &g = ctx->g;
-    int rc = build_receiver_cells(ctx);
+    const Geo geo = adjoint_geo(ctx);
+    int rc = build_receiver_cells(ctx, geo);
     if (rc != WAVE_OK)
         return rc;
     const size_t lb = level_bytes(ctx);
-    const size_t ab = (size_t)ctx->lay.elems * sizeof(double);
+    const size_t cells = (size_t)ctx->lap_plane * ctx->p.nz;
     for (int i = 0; i < 2; ++i)
         if (!g.phi[i]) {
             HIP_TRY(ctx, hipMalloc(&g.phi[i], lb));
         }
     if (!g.acc) {
-        HIP_TRY(ctx, hipMalloc(&g.acc, ab));
+        HIP_TRY(ctx, hipMalloc(&g.acc, (cells + 1) * sizeof(double)));
+    }
+    double *src_sum = g.acc + cells;
+    if (g.held != g.nseg - 1) {
+        // a repeated adjoint run: the adjoint fields are free until it starts
+        if ((rc = recompute_segment(ctx, g.nseg - 1, g.phi)) != WAVE_OK)
+            return rc;
     }
     HIP_TRY(ctx, hipMemsetAsync(g.phi[0], 0, lb, ctx->stream));
     HIP_TRY(ctx, hipMemsetAsync(g.phi[1], 0, lb, ctx->stream));
-    HIP_TRY(ctx, hipMemsetAsync(g.acc, 0, ab, ctx->stream));
-
-    // the source cell's thread in inject_receivers: the receiver cell that is
-    // also the source cell, else one past the receiver cells
+    HIP_TRY(ctx, hipMemsetAsync(src_sum, 0, sizeof(double), ctx->stream));
     src_term = src_term && g.has_src && ctx->src[0] >= 0;
-    long long src_off = 0;
-    int src_thread = g.ncells;
-    if (src_term) {
-        src_off = elem_offset(ctx->lay, ctx->src[0], ctx->src[1], ctx->src[2]);
-        for (int i = 0; i < g.ncells; ++i)
-            if (g.cell_off_host[i] == src_off)
-                src_thread = i;
-    }
 
-    const Geo geo = adjoint_geo(ctx);
-    // + K R^T (dJ/d traces, row m-1) into phi^m (and the source-cell term)
-    auto inject = [&](void *phi, int m) -> int {
-        const int threads = g.ncells + (src_term ? 1 : 0);
-        if (threads > 0) {
-            hipLaunchKernelGGL(inject_receivers, dim3((threads + 255) / 256), dim3(256), 0, ctx->stream,
-                               static_cast<float *>(phi), static_cast<const float *>(ctx->k), g.cell_off,
-                               g.cell_start, g.cell_rec, g.ncells,
-                               g.ncells > 0 ? trace_grad_dev + (size_t)(m - 1) * ctx->nrec : nullptr,
-                               src_term ? g.src + (m - 1) : nullptr, src_off, src_thread, g.acc);
+    // dJ/d traces of the step that made level m
+    auto row = [&](int m) {
+        return g.ncells > 0 ? trace_grad_dev + (size_t)(m - 1) * ctx->nrec : nullptr;
+    };
+    auto source = [&](const void *phi, int m) -> int {
+        if (src_term) {
+            hipLaunchKernelGGL(source_term, dim3(1), dim3(1), 0, ctx->stream, (const float *)phi,
+                               (const float *)ctx->k, elem_offset(ctx->lay, ctx->src[0], ctx->src[1], ctx->src[2]),
+                               (const float *)(g.src + (m - 1)), src_sum);
             HIP_TRY(ctx, hipGetLastError());
         }
         return WAVE_OK;
     };
-    // the level a^l, recomputing its segment from the checkpoint if needed
-    auto level = [&](int64_t l, const void **out) -> int {
+    // the Laplacian of level l, recomputing its segment if needed
+    auto laplacian = [&](int64_t l, void **out) -> int {
         const int seg = int(l / g.every);
         if (g.held != seg) {
-            const int64_t c0 = (int64_t)seg * g.every;
-            const int r = forward_segment(ctx, seg, int(std::min<int64_t>(g.every, g.nt - c0)) - 1, false);
+            void *const work[2] = {checkpoint_ptr(ctx, seg + 1, 0), checkpoint_ptr(ctx, seg + 1, 1)};
+            const int r = recompute_segment(ctx, seg, work);
             if (r != WAVE_OK)
                 return r;
         }
-        *out = level_ptr(ctx, seg, l);
+        *out = lap_ptr(ctx, seg, l);
         return WAVE_OK;
     };
-    const void *lev = nullptr;
-    void *A = g.phi[0], *B = g.phi[1];  // phi^{m+1}, phi^{m+2}
-    if (ctx->fuse_adjoint) {
-        // phi^nt, then for m = nt .. 2 one pass makes phi^{m-1} and adds the
-        // imaging term of phi^m; the term of phi^1 closes the sum
-        rc = enqueue_adjoint(ctx, geo, kAdj, A, B, B, nullptr);
+
+    // A = phi^m, B = phi^{m+1}; phi^{nt+1} = 0, and phi^nt holds only the
+    // last row's receivers
+    void *A = g.phi[0], *B = g.phi[1];
+    if (g.ncells > 0) {
+        hipLaunchKernelGGL(inject_receivers, dim3((g.ncells + 255) / 256), dim3(256), 0, ctx->stream,
+                           static_cast<float *>(A), static_cast<const float *>(ctx->k), g.cell_off, g.cell_start,
+                           g.cell_rec, g.ncells, row(g.nt));
+        HIP_TRY(ctx, hipGetLastError());
+    }
+    if ((rc = source(A, g.nt)) != WAVE_OK)
+        return rc;
+    // Step m makes phi^{m-1} and the imaging term of phi^m is due, which uses
+    // lap a^{m-1}.  A step can add the terms of both levels it reads, so the
+    // terms are added two at a time, every other step: the FP64 sum, 16 of
+    // the 40 bytes a cell such a step moves, is read and written half as
+    // often.  A term is not put off past the end of its segment, whose
+    // Laplacians the next one's replace.  Terms are added in the order of m
+    // whichever way.
+    bool first = true, due = false;  // due: the term of phi^{m+1} is still to be added
+    for (int m = g.nt; m >= 1; --m) {
+        void *lap = nullptr;
+        if ((rc = laplacian(m - 1, &lap)) != WAVE_OK)
+            return rc;
+        void *lap_far = due ? lap_ptr(ctx, g.held, m) : nullptr;
+        const bool put_off = ctx->fuse_adjoint && !due && m >= 2 && (m - 1) % g.every != 0;
+        if (m == 1 || !ctx->fuse_adjoint) {
+            if ((rc = enqueue_imaging(ctx, A, lap, B, lap_far, first)) != WAVE_OK)
+                return rc;
+            first = false;
+            if (m == 1)
+                break;
+            lap = nullptr;
+        }
+        rc = put_off ? enqueue_adjoint(ctx, geo, A, B, row(m - 1))
+                     : enqueue_adjoint(ctx, geo, A, B, row(m - 1), lap, lap_far, first);
         if (rc == WAVE_OK)
-            rc = inject(B, g.nt);
+            rc = source(B, m - 1);
         if (rc != WAVE_OK)
             return rc;
-        std::swap(A, B);  // A = phi^m, B = phi^{m+1}
-        for (int m = g.nt; m >= 2; --m) {
-            if ((rc = level(m - 1, &lev)) != WAVE_OK)
-                return rc;
-            rc = enqueue_adjoint(ctx, geo, kFus, A, B, B, g.acc, lev);
-            if (rc == WAVE_OK)
-                rc = inject(B, m - 1);
-            if (rc != WAVE_OK)
-                return rc;
-            std::swap(A, B);
-        }
-        if ((rc = level(0, &lev)) != WAVE_OK)
-            return rc;
-        if ((rc = enqueue_adjoint(ctx, geo, kImg, lev, A, nullptr, g.acc)) != WAVE_OK)
-            return rc;
-    } else {
-        for (int m = g.nt; m >= 1; --m) {
-            // phi^m = 2 G phi^{m+1} + K L G phi^{m+1} - G^2 phi^{m+2}, over phi^{m+2}
-            rc = enqueue_adjoint(ctx, geo, kAdj, A, B, B, nullptr);
-            if (rc != WAVE_OK)
-                return rc;
-            std::swap(A, B);
-            if ((rc = inject(A, m)) != WAVE_OK)
-                return rc;
-            // grad += (G phi^m / k) L a^{m-1}
-            if ((rc = level(m - 1, &lev)) != WAVE_OK)
-                return rc;
-            if ((rc = enqueue_adjoint(ctx, geo, kImg, lev, A, nullptr, g.acc)) != WAVE_OK)
-                return rc;
-        }
+        first = first && put_off;
+        due = put_off;
+        std::swap(A, B);
     }
     return WAVE_OK;
 }
 
-// dJ/dk (v == nullptr) or dJ/dv (k = (v dt)^2) from the accumulator into a
-// dense FP64 array.
+// dJ/dk (v == nullptr) or dJ/dv (k = (v dt)^2) from the FP64 sum into a dense
+// array.
 int adjoint_output(wave_ctx *ctx, double *grad_dev, int32_t accumulate, const float *v_dev, double dt)
 {
-    const long long n = (long long)ctx->p.nx * ctx->p.ny * ctx->p.nz;
-    hipLaunchKernelGGL(grad_to_dense, dim3((unsigned)std::min<long long>((n + 255) / 256, 8192)), dim3(256),
-                       0, ctx->stream, ctx->g.acc, grad_dev, ctx->p.nx, ctx->p.ny, ctx->p.nz,
-                       int(ctx->lay.pitch_x), int(ctx->lay.x_offset), (long long)ctx->lay.plane,
-                       accumulate ? 1 : 0, v_dev, 2.0 * dt * dt);
+    const wave_params_t &p = ctx->p;
+    const size_t cells = (size_t)ctx->lap_plane * p.nz;
+    const long long src =
+        ctx->src[0] >= 0 ? ((long long)ctx->src[0] * p.ny + ctx->src[1]) * p.nx + ctx->src[2] : -1;
+    const int bx = std::min(256, int(round_up(p.nx, 64)));
+    hipLaunchKernelGGL(grad_to_dense, dim3((p.nx + bx - 1) / bx, std::min(p.ny, 65535), std::min(p.nz, 65535)), dim3(bx), 0,
+                       ctx->stream, (const double *)ctx->g.acc, grad_dev, p.nx, p.ny, p.nz, ctx->lap_px, ctx->lap_plane,
+                       accumulate ? 1 : 0, v_dev, 2.0 * dt * dt, src, (const double *)(ctx->g.acc + cells));
     HIP_TRY(ctx, hipGetLastError());
     return WAVE_OK;
 }
@@ -2008,7 +2084,7 @@ int wave_grad_info(const wave_ctx *ctx, int32_t *nt, int32_t *every, int32_t *se
     if (segments)
         *segments = g.nseg;
     if (bytes)
-        *bytes = int64_t(g.slab_levels * level_bytes(ctx));
+        *bytes = int64_t(g.slab_bytes);
     return WAVE_OK;
 }
 

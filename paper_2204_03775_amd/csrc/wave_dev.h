@@ -73,12 +73,19 @@ struct StepArgs {
     // output field: == nxt for the in-place step (each cell is read, then
     // written, by the same thread), a separate level otherwise
     void *out;
-    // imaging: FP64 accumulator in the field layout (8-byte cells)
-    double *grad;
-    // fused adjoint step: the forward level whose Laplacian the imaging term needs
-    const void *aux;
-    // u-and-change storage: d^n on entry, d^{n+1} on exit (same cells, same thread)
+    // u-and-change storage: d^n on entry, d^{n+1} on exit (same cells, same
+    // thread).  FP32 gradient runs: kLap stores lap u^n here; kFus reads the
+    // Laplacian of the older level's imaging term, or NULL for one term
     void *dlt;
+    // kFus: the Laplacian of the centre level's imaging term, and the FP64 sum
+    // (overwritten by the launch that has `first` set).  Laplacians and sum
+    // are interior cells only: planes of lplane elements, rows of lpx
+    const void *aux;
+    double *grad;
+    int lpx;
+    int first;
+    long long lplane;
+    const int *inj_rec;  // adjoint: receivers by receiver cell (see inject_cells)
     // z-march direction of the tiled kernels: 0 up, 1 down.  Consecutive
     // launches alternate, so that a launch starts on the planes the one
     // before touched last, which the GPU's memory-side cache still holds.
@@ -87,17 +94,19 @@ struct StepArgs {
     int zdown;
 };
 
-// What a tiled launch computes (FP32 storage only for the last two):
+// What a tiled launch computes (FP32 storage only for the last three):
 //   kFwd  u^{n+1} = G (2 u^n - G u^{n-1} + k lap u^n) (+ source, receivers);
+//   kLap  kFwd, storing lap u^n as well;
 //   kAdj  the adjoint step phi^m = 2 psi + k lap psi - G^2 phi^{m+2} with
-//         psi = G phi^{m+1} (G applied to every loaded value);
-//   kImg  grad += (G phi / k) lap a: the imaging term of one adjoint step;
-//   kFus  kAdj from phi^m, phi^{m+1} together with the kImg term of phi^m
-//         and a = aux (the same arithmetic, bit for bit, in one pass).
+//         psi = G phi^{m+1} (G applied to every loaded value), then the
+//         receivers' trace derivatives added;
+//   kFus  kAdj making phi^{m-1} from phi^m and phi^{m+1}, which also adds to
+//         the FP64 sum the imaging terms (G phi / k) lap a of phi^m and, if
+//         asked, of phi^{m+1}.
 constexpr int kFwd = 0;
 constexpr int kAdj = 1;
-constexpr int kImg = 2;
-constexpr int kFus = 3;
+constexpr int kFus = 2;
+constexpr int kLap = 3;
 
 // A shot of a batched run.  `a` holds the shot's arguments with the buffer
 // roles of the run's first step (cur = u^{n0}, nxt = u^{n0-1}); step j of

@@ -12,6 +12,8 @@ template <int KIND, int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void step_tiled(StepArgs a);
 template <int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void step_tiled_cached(StepArgs a);
+template <bool CACHED, int TXV, int TY, int RY>
+__global__ __launch_bounds__(TXV *TY) void step_tiled_lap(StepArgs a);
 template <int MODE, int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void adjoint_tiled(StepArgs a);
 template <int KIND, int TXV, int TY, int RY>
@@ -39,8 +41,14 @@ __global__ __launch_bounds__(256) void k_range(const float *__restrict__ k, int 
 __global__ void inject_receivers(float *phi, const float *__restrict__ k,
                                  const long long *__restrict__ cell_off,
                                  const int *__restrict__ cell_start, const int *__restrict__ cell_rec,
-                                 int ncells, const float *__restrict__ tg_row, const float *__restrict__ s_val,
-                                 long long src_off, int src_thread, double *acc);
+                                 int ncells, const float *__restrict__ tg_row);
+__global__ void source_term(const float *phi, const float *k, long long off, const float *s, double *sum);
+__global__ __launch_bounds__(256) void imaging_terms(const float *__restrict__ phi_a, const float *__restrict__ lap_a,
+                                                     const float *__restrict__ phi_b, const float *__restrict__ lap_b,
+                                                     const float *__restrict__ k, const float *__restrict__ gx,
+                                                     const float *__restrict__ gy, const float *__restrict__ gz,
+                                                     int nx, int ny, int nz, int px, int x0, long long plane,
+                                                     int lpx, long long lplane, int first, double *sum);
 __global__ __launch_bounds__(256) void velocity_to_k(const float *__restrict__ v, long long n, double dt,
                                                     float *k);
 __global__ __launch_bounds__(1024) void misfit_kernel(const float *__restrict__ tr,
@@ -50,9 +58,9 @@ __global__ __launch_bounds__(256) void count_nonfinite(const void *__restrict__ 
                                                       int ny, int nz, int px, int x0, long long plane,
                                                       const float *__restrict__ traces, long long n,
                                                       int *out);
-__global__ __launch_bounds__(256) void grad_to_dense(const double *__restrict__ acc, double *dense, int nx,
-                                                    int ny, int nz, int px, int x0, long long plane,
-                                                    int accumulate, const float *__restrict__ v,
-                                                    double two_dt2);
+__global__ __launch_bounds__(256) void grad_to_dense(const double *__restrict__ sum, double *dense, int nx,
+                                                    int ny, int nz, int lpx, long long lplane, int accumulate,
+                                                    const float *__restrict__ v, double two_dt2, long long src,
+                                                    const double *__restrict__ src_sum);
 
 }  // namespace wavek

@@ -403,6 +403,26 @@ __device__ __forceinline__ void sample_receivers(const StepArgs &a, int r0, int 
     }
 }
 
+// The adjoint step's counterpart: once the tile column holds phi^{m-1}, add
+// k * (sum of the trace derivatives of row m-2) at the receiver cells this
+// work-group owns (rec_start ranges over the cells: rec_off the cell's
+// offset, rec_idx its range in inj_rec, the receivers in a fixed order).
+// A launch of its own took 4.7 us a step plus the gap before it.
+__device__ __forceinline__ void inject_cells(const StepArgs &a, int r0, int r1, int tid, int nt)
+{
+    if (r0 == r1)
+        return;
+    __syncthreads();
+    for (int c = r0 + tid; c < r1; c += nt) {
+        float s = 0.f;
+        for (int i = a.rec_idx[c]; i < a.rec_idx[c + 1]; ++i)
+            s += a.trace_row[a.inj_rec[i]];
+        const long long o = a.rec_off[c];
+        float *p = static_cast<float *>(a.out) + o;
+        *p = fmaf(static_cast<const float *>(a.k)[o], s, *p);
+    }
+}
+
 // Calls f(integral_constant<int, S>) for S = B, B+1, ... < E while f
 // returns true: a loop unrolled at compile time, so every index that
 // depends on S is a constant and register arrays stay in registers.
@@ -433,11 +453,10 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     constexpr unsigned EB = Store<KIND>::bytes;
     constexpr bool SCALED = Store<KIND>::scaled;
     constexpr bool UV = Store<KIND>::uv;          // second input is d^n, also written
-    constexpr bool FUS = MODE == kFus;            // adjoint step + imaging term of the step after it
+    constexpr bool LAP = MODE == kLap;            // forward step that also stores lap u^n
+    constexpr bool FUS = MODE == kFus;            // adjoint step + the imaging terms of the levels it reads
     constexpr bool ADJ = MODE == kAdj || FUS;     // the stencil field is phi, scaled by G on load
-    constexpr bool IMG = MODE == kImg;
-    constexpr bool GRAD = IMG || FUS;             // adds an imaging term to the FP64 accumulator
-    static_assert(MODE == kFwd || KIND == WAVE_F32, "adjoint and imaging steps are FP32 only");
+    static_assert(MODE == kFwd || KIND == WAVE_F32, "Laplacian stores and adjoint steps are FP32 only");
     // load policies of the wave fields (k never changes during a run);
     // CACHED: u^{n-1} and k too keep the default policy, for grids whose
     // fields fit in the memory-side cache together.  The step change d^n of
@@ -450,8 +469,6 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     constexpr int PS = ((CACHED || UV) ? kKeep : kStream) | (COH ? kCoh : 0);
     constexpr int PKK = CACHED ? kKeep : kStream;
     __shared__ f4 lds[2][LH][LW];
-    // second stencil field (the forward level of the imaging term), fused mode only
-    __shared__ f4 lds2[FUS ? 2 : 1][FUS ? LH : 1][FUS ? LW : 1];
 
     const int tx = lid % a.ntx;
     const int rest = lid / a.ntx;
@@ -486,7 +503,6 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     // hold zero, and their loads are masked so that they return zero without
     // reading memory.
     const bool col_interior = x < a.nx;
-    const bool col_full = x + 3 < a.nx;
     // whether this tile holds the grid's ragged last group (uniform)
     const bool ragged = (a.nx & 3) != 0 && tx == a.ntx - 1;
 
@@ -584,7 +600,7 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     }
     const float sval = src_r >= 0 ? src_value(a) * sc.out_inv : 0.f;
 
-    // this work-group's receivers
+    // this work-group's receivers (adjoint: receiver cells)
     int rec0 = 0, rec1 = 0;
     if (a.trace_row) {
         rec0 = a.rec_start[lid];
@@ -601,7 +617,6 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
         return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gz_r, 4u * unsigned(z), 0, 0));
     };
     f4 q[QS][RY];
-    f4 q2[FUS ? QS : 1][RY];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int zi = zp(i - 4);
@@ -609,12 +624,6 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
 #pragma unroll
         for (int r = 0; r < RY; ++r)
             q[i][r] = load4<KIND, PK>(rc, own_ld[r], 1.f);
-        if constexpr (FUS) {
-            const __amdgpu_buffer_rsrc_t ra = stencil_plane_rsrc(a.aux, pbytes, zi, a.nz);
-#pragma unroll
-            for (int r = 0; r < RY; ++r)
-                q2[i][r] = load4<KIND, PK>(ra, own_ld[r], 1.f);
-        }
         if constexpr (ADJ) {
             const float gzi = gz_at(zi);
 #pragma unroll
@@ -628,7 +637,24 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     // values of the next plane, loaded one plane ahead into the set of the
     // other parity (no copies, so no wait before the next loads are issued)
     Raw4<KIND> pv[2][RY], kv[2][RY], hv[2][HPT];
-    f4 hv2[FUS ? 2 : 1][FUS ? HPT : 1];
+    // fused mode: the Laplacians of the two forward levels, and the sum
+    Raw4<WAVE_F32> lv[FUS ? 2 : 1][2][RY];
+    dv2 gacc[FUS ? 2 : 1][RY][2];
+    const int lbytes = (int)(a.lplane * 4);
+    const bool two = FUS && a.dlt != nullptr;  // also the term of the level before (phi^{m+1})
+    const bool keep_sum = FUS && !a.first;     // the first term overwrites the accumulator
+    unsigned own_lap[RY];
+#pragma unroll
+    for (int r = 0; r < RY; ++r)
+        own_lap[r] = row_int[r] ? 4u * unsigned(row[r] * a.lpx + x) : kOff;
+    auto lap_rsrc = [&](const void *f, int z, bool live) {
+        const char *p = reinterpret_cast<const char *>(f) + (long long)z * lbytes;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p), (short)0, live ? lbytes : 0, kRsrcWord3);
+    };
+    // an accumulator cell group is two aligned 16-byte pairs
+    auto sum_at = [&](int z, int r) {
+        return reinterpret_cast<dv2 *>(a.grad + (long long)z * a.lplane + own_lap[r] / 4);
+    };
     float gzv[2], gzq[2];  // g_z of the plane and (adjoint) of the queue plane four positions on
     // Addresses of the planes being loaded and written.  16-bit storage
     // advances them by one plane per iteration, two scalar adds per field in
@@ -667,14 +693,22 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
         for (int h = 0; h < HPT; ++h)
             hv[set][h] = load_raw4<KIND, PK>(rh, h_b[h]);
         if constexpr (FUS) {
-            const __amdgpu_buffer_rsrc_t raq = stencil_plane_rsrc(a.aux, pbytes, zp(l + 4), a.nz);
-            const __amdgpu_buffer_rsrc_t rah = plane_rsrc(a.aux, pbytes, z);
+            const __amdgpu_buffer_rsrc_t r0 = lap_rsrc(a.aux, z, true), r1 = lap_rsrc(a.dlt, z, two);
 #pragma unroll
-            for (int r = 0; r < RY; ++r)
-                q2[slot][r] = load4<KIND, PK>(raq, own_ld[r], 1.f);
-#pragma unroll
-            for (int h = 0; h < HPT; ++h)
-                hv2[set][h] = load4<KIND, PK>(rah, h_b[h], 1.f);
+            for (int r = 0; r < RY; ++r) {
+                lv[set][0][r] = load_raw4<WAVE_F32, kStream>(r0, own_lap[r]);
+                lv[set][1][r] = load_raw4<WAVE_F32, kStream>(r1, own_lap[r]);
+                // Each cell of the sum is read and written once per launch, but
+                // with the z-march reversed every launch the planes a launch
+                // touches last are the first the next one touches: the default
+                // cache policy lets the memory-side cache serve part of it
+                gacc[set][r][0] = gacc[set][r][1] = dv2{0.0, 0.0};
+                if (keep_sum && row_int[r]) {
+                    const dv2 *gp = sum_at(z, r);
+                    gacc[set][r][0] = gp[0];
+                    gacc[set][r][1] = gp[1];
+                }
+            }
         }
         gzv[set] = gz_at(z);
         if constexpr (ADJ)
@@ -700,24 +734,6 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
             const int z = zp(l);
             constexpr int cur_set = s & 1;
             prefetch(l + 1, (s + 9) % QS, cur_set ^ 1);
-            // imaging modes: this plane's accumulator values, loaded before
-            // the arithmetic so that their latency overlaps it.  Each cell is
-            // read and written once per step, but with the z-march reversed
-            // every launch the planes a launch touches last are the first
-            // the next one touches, so the accumulator keeps the default
-            // cache policy and the memory-side cache serves part of it
-            dv2 gacc[GRAD ? RY : 1][2] = {};
-            if constexpr (GRAD) {
-#pragma unroll
-                for (int r = 0; r < RY; ++r)
-                    if (col_full && row_int[r]) {
-                        const dv2 *gp = reinterpret_cast<const dv2 *>(
-                            a.grad + (long long)(z + kGhost) * a.plane + own_in[r] / EB);
-                        gacc[r][0] = gp[0];
-                        gacc[r][1] = gp[1];
-                    }
-            }
-
             if constexpr (ADJ) {
                 // psi = G phi: the plane that just entered the queue (four positions on)
                 // and this plane's halo
@@ -744,16 +760,6 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                 if (h_lds[h] >= 0)
                     L[h_lds[h]] = hd;
             }
-            f4 *L2 = &lds2[FUS ? b : 0][0][0];
-            if constexpr (FUS) {
-#pragma unroll
-                for (int r = 0; r < RY; ++r)
-                    L2[(4 + ly * RY + r) * LW + lx + 1] = q2[(s + 4) % QS][r];
-#pragma unroll
-                for (int h = 0; h < HPT; ++h)
-                    if (h_lds[h] >= 0)
-                        L2[h_lds[h]] = hv2[cur_set][h];
-            }
             __syncthreads();
 
             // y taps: LDS rows ly*RY - 4 .. ly*RY + RY + 3 of this column,
@@ -766,17 +772,6 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                 else
                     ycol[j] = L[(ly * RY + j) * LW + lx + 1];
             }
-            f4 ycol2[FUS ? RY + 8 : 1];
-            if constexpr (FUS) {
-#pragma unroll
-                for (int j = 0; j < RY + 8; ++j) {
-                    if (j >= 4 && j < 4 + RY)
-                        ycol2[j] = q2[(s + 4) % QS][j - 4];
-                    else
-                        ycol2[j] = L2[(ly * RY + j) * LW + lx + 1];
-                }
-            }
-
             const __amdgpu_buffer_rsrc_t ro = INC ? rsrc_at(po, pbytes) : plane_rsrc(a.out, pbytes, z);
             const __amdgpu_buffer_rsrc_t rdl = rsrc_at(UV ? pd : po, pbytes);
             if constexpr (INC)
@@ -797,19 +792,8 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                     xs[4 + e] = ctr.v[e];
                     xs[8 + e] = xr.v[e];
                 }
-                float xs2[FUS ? 12 : 1];
-                if constexpr (FUS) {
-                    const f4 xl2 = L2[(4 + ly * RY + r) * LW + lx];
-                    const f4 xr2 = L2[(4 + ly * RY + r) * LW + lx + 2];
-                    const f4 ctr2 = q2[(s + 4) % QS][r];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        xs2[e] = xl2.v[e];
-                        xs2[4 + e] = ctr2.v[e];
-                        xs2[8 + e] = xr2.v[e];
-                    }
-                }
-                f4 out, img;
+                f4 out, lapv;
+                float img[FUS ? 2 : 1][4];  // imaging terms: of phi^m (centre) and of phi^{m+1}
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float lap;
@@ -838,28 +822,18 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                         }
                     }
                     const float g = gxv.v[e] * gyv[r] * gzv[cur_set];
-                    if constexpr (IMG) {
-                        // imaging term (G phi / k) lap a
-                        out.v[e] = (g * pvd.v[e]) / kvd.v[e] * lap;
-                    } else if constexpr (ADJ) {
+                    if constexpr (LAP)
+                        lapv.v[e] = lap;
+                    if constexpr (ADJ) {
                         const float t = fmaf(kvd.v[e], lap, 2.f * ctr.v[e]);
                         out.v[e] = fmaf(-g * g, pvd.v[e], t);
                         if constexpr (FUS) {
-                            // imaging term of the step after this one: the
-                            // centre already holds G phi, bit for bit g * phi
-                            const float u2b = 2.f * xs2[4 + e];
-                            float lap2 = 0.f;
-#pragma unroll
-                            for (int m = 1; m <= 4; ++m) {
-                                lap2 = fmaf(c.cx[m - 1], (xs2[4 + e + m] + xs2[4 + e - m]) - u2b, lap2);
-                                lap2 = fmaf(c.cy[m - 1],
-                                            (ycol2[4 + r + m].v[e] + ycol2[4 + r - m].v[e]) - u2b, lap2);
-                                lap2 = fmaf(c.cz[m - 1],
-                                            (q2[(s + 4 + m) % QS][r].v[e] + q2[(s + 4 - m + QS) % QS][r].v[e]) -
-                                                u2b,
-                                            lap2);
+                            // (G phi / k) lap a; the centre already holds G phi
+                            img[0][e] = ctr.v[e] / kvd.v[e] * __uint_as_float(lv[cur_set][0][r][e]);
+                            if (two) {
+                                keep_branch();
+                                img[1][e] = (g * pvd.v[e]) / kvd.v[e] * __uint_as_float(lv[cur_set][1][r][e]);
                             }
-                            img.v[e] = ctr.v[e] / kvd.v[e] * lap2;
                         }
                     } else {
                         float t, pe;
@@ -877,35 +851,24 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                         out.v[e] = g * t;
                     }
                 }
-                // the accumulator has the field layout with 8-byte cells, so
-                // a full 4-cell group is two aligned 16-byte pairs
-                auto add_grad = [&](const f4 &t) __attribute__((always_inline)) {
-                    if (col_full) {
-                        if (row_int[r]) {
-                            dv2 *gp = reinterpret_cast<dv2 *>(a.grad + (long long)(z + kGhost) * a.plane +
-                                                              own_in[r] / EB);
-                            dv2 g0 = gacc[r][0], g1 = gacc[r][1];
-                            g0.x += (double)t.v[0];
-                            g0.y += (double)t.v[1];
-                            g1.x += (double)t.v[2];
-                            g1.y += (double)t.v[3];
-                            gp[0] = g0;
-                            gp[1] = g1;
-                        }
-                    } else if (row_int[r]) {
-                        double *gp = a.grad + (long long)(z + kGhost) * a.plane + own_in[r] / EB;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (x + e < a.nx)
-                                gp[e] += (double)t.v[e];
+                if constexpr (FUS) {
+                    // the older level's term first, as one term per launch would add them
+                    dv2 g0 = gacc[cur_set][r][0], g1 = gacc[cur_set][r][1];
+                    if (two) {
+                        keep_branch();
+                        g0 += dv2{(double)img[1][0], (double)img[1][1]};
+                        g1 += dv2{(double)img[1][2], (double)img[1][3]};
                     }
-                };
-                if constexpr (IMG) {
-                    add_grad(out);
-                    continue;
+                    g0 += dv2{(double)img[0][0], (double)img[0][1]};
+                    g1 += dv2{(double)img[0][2], (double)img[0][3]};
+                    if (row_int[r]) {
+                        dv2 *gp = sum_at(z, r);
+                        gp[0] = g0;
+                        gp[1] = g1;
+                    }
                 }
-                if constexpr (FUS)
-                    add_grad(img);
+                if constexpr (LAP)
+                    store4<WAVE_F32>(lap_rsrc(a.dlt, z, true), own_lap[r], lapv, 1.f);
                 if (z == a.src_z) {
                     keep_branch();  // one plane of the grid
                     if (src_r == r) {
@@ -951,7 +914,10 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
 
     if constexpr (SCALED)
         fold_max(a, lid, tmax * sc.out);
-    sample_receivers<KIND>(a, rec0, rec1, tid, NT, sc.out);
+    if constexpr (ADJ)
+        inject_cells(a, rec0, rec1, tid, NT);
+    else
+        sample_receivers<KIND>(a, rec0, rec1, tid, NT, sc.out);
 }
 
 template <int KIND, int TXV, int TY, int RY>
@@ -974,6 +940,23 @@ __global__ __launch_bounds__(TXV *TY) void step_tiled_cached(StepArgs a)
     if (lid >= a.nwg)
         return;
     tile_step<WAVE_F32, TXV, TY, RY, kFwd, false, true>(a, lid);
+}
+
+// The FP32 step that also stores the Laplacian it computes: the forward run
+// of a gradient, whose imaging terms then read a value per cell instead of a
+// second stencil field (written with the streaming policy: the adjoint run
+// reads it once, many steps later).  Fields in or out of the memory-side
+// cache as above.  With the forward levels themselves stored, the adjoint
+// step carried two stencil fields in 237 registers and two LDS tiles: 105 us
+// at 256^3 for one imaging term.  Now the adjoint steps are bound by
+// bandwidth: 256^3 x 150 gradient 22.6 -> 18.6 ms.
+template <bool CACHED, int TXV, int TY, int RY>
+__global__ __launch_bounds__(TXV *TY) void step_tiled_lap(StepArgs a)
+{
+    const int lid = logical_wg();
+    if (lid >= a.nwg)
+        return;
+    tile_step<WAVE_F32, TXV, TY, RY, kLap, false, CACHED>(a, lid);
 }
 
 template <int MODE, int TXV, int TY, int RY>
@@ -1265,6 +1248,8 @@ __global__ __launch_bounds__(256) void step_naive(StepArgs a)
             v += src_value(a) * sc.out_inv;
         if constexpr (KIND == WAVE_F32) {
             static_cast<float *>(a.out)[p] = v;
+            if (a.dlt)  // gradient runs: the Laplacian's own layout
+                static_cast<float *>(a.dlt)[z * a.lplane + (long long)y * a.lpx + x] = lap;
         } else {
             static_cast<unsigned short *>(a.out)[p] = (unsigned short)Store<KIND>::enc(v);
             if constexpr (Store<KIND>::uv)
