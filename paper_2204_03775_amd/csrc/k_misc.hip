@@ -35,7 +35,9 @@ __global__ void source_term(const float *phi, const float *k, long long off, con
 
 // Imaging terms of one or two adjoint levels as a pass of their own: sum (+)=
 // (G phi_b / k) lap_b, then + (G phi_a / k) lap_a (the older level b first;
-// phi_b may be NULL).  Rows of four-cell groups: one thread per group.
+// phi_b may be NULL).  One thread per group of four cells, 16-byte accesses
+// throughout: the groups of every array start on 16 bytes, and a ragged last
+// group's cells past nx hold padding nobody reads.
 __global__ __launch_bounds__(256) void imaging_terms(const float *__restrict__ phi_a, const float *__restrict__ lap_a,
                                                      const float *__restrict__ phi_b, const float *__restrict__ lap_b,
                                                      const float *__restrict__ k, const float *__restrict__ gx,
@@ -43,22 +45,39 @@ __global__ __launch_bounds__(256) void imaging_terms(const float *__restrict__ p
                                                      int nx, int ny, int nz, int px, int x0, long long plane,
                                                      int lpx, long long lplane, int first, double *sum)
 {
+    typedef double dv2 __attribute__((ext_vector_type(2)));
     const int nxq = (nx + 3) / 4;
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= ny * nxq)
         return;
     const int y = q / nxq, x = 4 * (q - y * nxq);
+    float gxy[4];
+    for (int e = 0; e < 4; ++e)
+        gxy[e] = x + e < nx ? gx[x + e] * gy[y] : 0.f;
+    auto load = [](const float *p) { return *reinterpret_cast<const f4 *>(p); };
     for (int z = blockIdx.z; z < nz; z += gridDim.z) {
         const long long f = (long long)(z + kGhost) * plane + (long long)(y + kGhost) * px + x0 + x;
         const long long l = z * lplane + (long long)y * lpx + x;
-        for (int e = 0; e < 4 && x + e < nx; ++e) {
-            const float g = gx[x + e] * gy[y] * gz[z];
-            double t = first ? 0.0 : sum[l + e];
-            if (phi_b)
-                t += (double)((g * phi_b[f + e]) / k[f + e] * lap_b[l + e]);
-            t += (double)((g * phi_a[f + e]) / k[f + e] * lap_a[l + e]);
-            sum[l + e] = t;
+        const f4 kk = load(k + f), pa = load(phi_a + f), la = load(lap_a + l);
+        f4 pb{}, lb{};
+        if (phi_b) {
+            pb = load(phi_b + f);
+            lb = load(lap_b + l);
         }
+        dv2 *s = reinterpret_cast<dv2 *>(sum + l);
+        double t[4] = {0.0, 0.0, 0.0, 0.0};
+        if (!first) {
+            const dv2 s0 = s[0], s1 = s[1];
+            t[0] = s0.x, t[1] = s0.y, t[2] = s1.x, t[3] = s1.y;
+        }
+        for (int e = 0; e < 4; ++e) {
+            const float g = gxy[e] * gz[z];
+            if (phi_b)
+                t[e] += (double)((g * pb.v[e]) / kk.v[e] * lb.v[e]);
+            t[e] += (double)((g * pa.v[e]) / kk.v[e] * la.v[e]);
+        }
+        s[0] = dv2{t[0], t[1]};
+        s[1] = dv2{t[2], t[3]};
     }
 }
 

@@ -381,6 +381,34 @@ double tile_fit(int nx, int ny, int tx, int tyr)
     return lanes * even;
 }
 
+// The FP32 tile shape, of n candidates, with the highest fit times the chunk
+// rule's round efficiency times its weight (the first on a tie), and its
+// z-chunk.
+struct Cand32 {
+    int v;
+    double weight;
+};
+
+int plan32(int nx, int ny, int nz, const Cand32 *cand, int n, int *zc)
+{
+    double best = -1.0;
+    int v = cand[0].v;
+    for (int i = 0; i < n; ++i) {
+        const Variant &C = kVariants[cand[i].v];
+        const int tx = 4 * C.txv, tyr = C.ty * C.ry;
+        const long long tiles = (long long)((nx + tx - 1) / tx) * ((ny + tyr - 1) / tyr);
+        double eff = 0.0;
+        const int z = fill_rounds_chunk(tiles, nz, kMinChunk, round_workgroups(WAVE_F32, cand[i].v), &eff);
+        eff *= tile_fit(nx, ny, tx, tyr) * cand[i].weight;
+        if (eff > best * (1.0 + 1e-9)) {
+            best = eff;
+            v = cand[i].v;
+            *zc = z;
+        }
+    }
+    return v;
+}
+
 // Tile shape and z-chunk of a 16-bit step on a grid of 2^22 cells or more:
 // the pair with the least
 //     T = 3 us + tau R (zc + 3) u^alpha,   R = ceil(nwg / cap), u = nwg / (R cap)
@@ -444,30 +472,15 @@ Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
     if (v == 0 && !large) {
         v = kSmallVariant;
     } else if (v == 0 && kind == WAVE_F32) {
-        // FP32: 128 x 16 or 256 x 8 tiles, by fit times the chunk rule's
-        // round efficiency.  Where at least 95 % of a 256-wide tile's lanes
-        // lie in the grid the wide tiles get 2 %: on full tiles, where both
-        // shapes score the same, they are 1.5-3 % faster (512^3: 323 against
-        // 337 us; 256^3: 38.9 against 39.8).
-        v = double(nx) / (256.0 * ((nx + 255) / 256)) < 0.95 ? kAutoNarrowVariant : kAutoVariant;
-        double best = -1.0;
-        for (const int cand : {kAutoNarrowVariant, kAutoVariant}) {
-            if (zchunk > 0)
-                break;
-            const Variant &C = kVariants[cand];
-            const int tx = 4 * C.txv, tyr = C.ty * C.ry;
-            const long long tiles = (long long)((nx + tx - 1) / tx) * ((ny + tyr - 1) / tyr);
-            double eff = 0.0;
-            const int z = fill_rounds_chunk(tiles, nz, kMinChunk, round_workgroups(kind, cand), &eff);
-            eff *= tile_fit(nx, ny, tx, tyr);
-            if (cand == kAutoVariant && double(nx) / (256.0 * ((nx + 255) / 256)) >= 0.95)
-                eff *= 1.02;
-            if (eff > best * (1.0 + 1e-9)) {
-                best = eff;
-                v = cand;
-                zc = z;
-            }
-        }
+        // FP32: 128 x 16 or 256 x 8 tiles.  Where at least 95 % of a 256-wide
+        // tile's lanes lie in the grid the wide tiles get 2 %: on full tiles,
+        // where both shapes score the same, they are 1.5-3 % faster (512^3:
+        // 323 against 337 us; 256^3: 38.9 against 39.8).
+        const bool wide = double(nx) / (256.0 * ((nx + 255) / 256)) >= 0.95;
+        const Cand32 cand[] = {{kAutoNarrowVariant, 1.0}, {kAutoVariant, wide ? 1.02 : 1.0}};
+        v = wide ? kAutoVariant : kAutoNarrowVariant;
+        if (zc <= 0)
+            v = plan32(nx, ny, nz, cand, 2, &zc);
     } else if (v == 0) {
         // 16-bit.  Two levels on grids of 2^27 cells or more take 128 x 16
         // tiles of two rows in two work-groups per CU: BF16 512^3 187 us
@@ -778,19 +791,24 @@ Geo ctx_geo(const wave_ctx *c)
     return g;
 }
 
-// The adjoint and imaging steps use the context's tiling when one was
-// configured, else their own automatic choice: the fused pass holds two
-// stencil fields, and at 256 x 8 tiles it needs more than the 256 registers
-// two waves per SIMD allow (it spills), while 128 x 16 tiles fit (241).
-constexpr int kAdjointAutoVariant = 6;  // t128x16_r1 for grids of >= 2^22 cells
-
+// The adjoint steps use the context's tiling when one was configured, else
+// their own automatic choice, by the FP32 rule over three tile shapes: the
+// kernel with imaging terms takes 180 registers, so its 64 x 16 tiles run two
+// work-groups per CU.  Against every tile shape and chunk on 10 grids of
+// 2^22 .. 2^24 cells the choice averages 1.005 times the fastest plan
+// (128 x 16 tiles with chunks of 32 planes and more averaged 1.46 times it:
+// 203x181x157 63.9 -> 40.2 us a step, 310x251x83 76.1 -> 42.7).
 Geo adjoint_geo(const wave_ctx *c)
 {
     if (c->variant != 0 && c->v_used != kNaive)
         return ctx_geo(c);
-    const long long pts = (long long)c->p.nx * c->p.ny * c->p.nz;
-    return plan_geo(c->p.nx, c->p.ny, c->p.nz, WAVE_F32, pts >= (1ll << 22) ? kAdjointAutoVariant : kSmallVariant,
-                    0);
+    const wave_params_t &p = c->p;
+    if ((long long)p.nx * p.ny * p.nz < (1ll << 22))
+        return plan_geo(p.nx, p.ny, p.nz, WAVE_F32, kSmallVariant, 0);
+    const Cand32 cand[] = {{kAutoNarrowVariant, 1.0}, {kAutoVariant, 0.95}, {kSmallVariant, 0.94}};
+    int zc = 0;
+    const int v = plan32(p.nx, p.ny, p.nz, cand, 3, &zc);
+    return plan_geo(p.nx, p.ny, p.nz, WAVE_F32, v, zc);
 }
 
 // One adjoint step: phi^{m-1} over `far` (phi^{m+1}) from `near` (phi^m) and
