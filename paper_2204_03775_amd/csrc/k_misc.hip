@@ -3,6 +3,7 @@
 // reduction and gradient output.
 
 #include "wave_dev.h"
+#include "wave_kernels.h"
 
 namespace wavek {
 
@@ -95,17 +96,35 @@ __global__ __launch_bounds__(256) void velocity_to_k(const float *__restrict__ v
 
 // misfit = 0.5 sum (traces - d_obs)^2 in FP64 (one work-group, fixed
 // summation order, differences taken exactly); residual = traces - d_obs
-// rounded to FP32 when requested.
+// rounded to FP32 when requested.  One work-group's loop is a chain of memory
+// latencies, so every thread has eight values of each array in flight.
 __global__ __launch_bounds__(1024) void misfit_kernel(const float *__restrict__ tr,
                                                       const float *__restrict__ obs, long long n,
                                                       float *residual, double *out)
 {
+    constexpr int U = 8;
     __shared__ double part[1024];
     double acc = 0.0;
-    for (long long i = threadIdx.x; i < n; i += blockDim.x) {
-        const double r = (double)tr[i] - (double)obs[i];  // exact
+    long long i = threadIdx.x;
+    for (; i + (U - 1) * 1024ll < n; i += U * 1024ll) {
+        float a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a[u] = tr[i + u * 1024ll];
+            b[u] = obs[i + u * 1024ll];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double r = (double)a[u] - (double)b[u];  // exact
+            if (residual)
+                residual[i + u * 1024ll] = (float)r;  // == the FP32 difference
+            acc += r * r;
+        }
+    }
+    for (; i < n; i += 1024) {
+        const double r = (double)tr[i] - (double)obs[i];
         if (residual)
-            residual[i] = (float)r;  // == the FP32 difference
+            residual[i] = (float)r;
         acc += r * r;
     }
     part[threadIdx.x] = acc;
@@ -157,45 +176,44 @@ __global__ __launch_bounds__(256) void zero_ints(int *p, long long n)
         p[i] = 0;
 }
 
-// Max, min and a non-finite flag of an FP32 k over the interior, as float
-// bit patterns (valid for non-negative values; negatives raise the flag).
+// Max and a non-finite (or negative) flag of an FP32 k over the interior, as
+// float bit patterns (valid for non-negative values; negatives raise the
+// flag).  One atomic per block at most, and none where it would change
+// nothing: atomics on one address are served one after another (the former
+// three per block of 1024 blocks took 39 us on the smallest grid).
 __global__ __launch_bounds__(256) void k_range(const float *__restrict__ k, int nx, int ny, int nz,
                                                int px, int x0, long long plane, unsigned *out)
 {
-    __shared__ unsigned smax[256], smin[256], sbad[256];
-    unsigned mx = 0u, mn = 0x7f800000u, bad = 0u;
-    const long long n = (long long)nx * ny * nz;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(i % nx);
-        const int y = (int)((i / nx) % ny);
-        const int z = (int)(i / ((long long)nx * ny));
-        const float v = k[(long long)(z + kGhost) * plane + (long long)(y + kGhost) * px + x0 + x];
-        if (!(v >= 0.f) || !(v < INFINITY)) {
-            bad = 1u;
-        } else {
-            const unsigned b = __float_as_uint(v);
-            mx = max(mx, b);
-            mn = min(mn, b);
+    __shared__ unsigned smax[256], sbad[256];
+    unsigned mx = 0u, bad = 0u;
+    for_interior_groups(nx, ny, nz, [&](int z, int y, int x, int n) {
+        const float *p = k + (long long)(z + kGhost) * plane + (long long)(y + kGhost) * px + x0 + x;
+        const f4 v = *reinterpret_cast<const f4 *>(p);
+        for (int e = 0; e < 4; ++e) {
+            if (e >= n)
+                continue;  // right-ghost cells: ignored
+            if (!(v.v[e] >= 0.f) || !(v.v[e] < INFINITY))
+                bad = 1u;
+            else
+                mx = max(mx, __float_as_uint(v.v[e]));
         }
-    }
-    const int t = threadIdx.x;
+    });
+    const int t = threadIdx.y * blockDim.x + threadIdx.x;
     smax[t] = mx;
-    smin[t] = mn;
     sbad[t] = bad;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
         if (t < s) {
             smax[t] = max(smax[t], smax[t + s]);
-            smin[t] = min(smin[t], smin[t + s]);
             sbad[t] |= sbad[t + s];
         }
         __syncthreads();
     }
     if (t == 0) {
-        atomicMax(&out[0], smax[0]);
-        atomicMin(&out[1], smin[0]);
-        atomicOr(&out[2], sbad[0]);
+        if (smax[0] > out[0])
+            atomicMax(&out[0], smax[0]);
+        if (sbad[0])
+            atomicOr(&out[1], sbad[0]);
     }
 }
 
@@ -206,23 +224,23 @@ __global__ __launch_bounds__(256) void count_nonfinite(const void *__restrict__ 
                                                       const float *__restrict__ traces, long long n,
                                                       int *out)
 {
-    const long long cells = (long long)nx * ny * nz;
-    const long long stride = (long long)gridDim.x * blockDim.x;
     int bad_f = 0, bad_t = 0;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < cells; i += stride) {
-        const int x = (int)(i % nx);
-        const int y = (int)((i / nx) % ny);
-        const int z = (int)(i / ((long long)nx * ny));
+    for_interior_groups(nx, ny, nz, [&](int z, int y, int x, int cells) {
         const long long p = (long long)(z + kGhost) * plane + (long long)(y + kGhost) * px + x0 + x;
         if (kind == WAVE_F32) {
-            bad_f += !isfinite(static_cast<const float *>(field)[p]);
+            const f4 v = *reinterpret_cast<const f4 *>(static_cast<const float *>(field) + p);
+            for (int e = 0; e < 4; ++e)
+                bad_f += e < cells && !isfinite(v.v[e]);
         } else {
-            const unsigned b = static_cast<const unsigned short *>(field)[p];
-            const unsigned e = (kind == WAVE_F16 || kind == WAVE_F16_UV) ? 0x7c00u : 0x7f80u;
-            bad_f += (b & e) == e;  // all-ones exponent: infinity or NaN
+            const ushort4 v = *reinterpret_cast<const ushort4 *>(static_cast<const unsigned short *>(field) + p);
+            const unsigned b[4] = {v.x, v.y, v.z, v.w};
+            const unsigned m = (kind == WAVE_F16 || kind == WAVE_F16_UV) ? 0x7c00u : 0x7f80u;
+            for (int e = 0; e < 4; ++e)
+                bad_f += e < cells && (b[e] & m) == m;  // all-ones exponent: infinity or NaN
         }
-    }
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+    });
+    const long long t = ((long long)blockIdx.x * blockDim.y + threadIdx.y) * blockDim.x + threadIdx.x;
+    for (long long i = t; i < n; i += (long long)gridDim.x * blockDim.x * blockDim.y)
         bad_t += !isfinite(traces[i]);
     if (bad_f)
         atomicAdd(&out[0], bad_f);

@@ -145,8 +145,11 @@ struct Geo {
 
 }  // namespace
 
-// ints of a context's scale history: a line of exponents, then 4 levels' max slots
+// ints of a context's scale history: a line that starts with the exponents,
+// then 4 levels' max slots; the line also holds two counters of the library's
+// own checks (the range of k at init, wave_check)
 constexpr int kRingInts = kMaxStride + 4 * kMaxSlots * kMaxStride;
+constexpr int kRingCounters = 8;
 
 // State of the gradient computation (FP32 storage): the checkpoints and the
 // store of the last checkpointed forward run and the adjoint fields, in the
@@ -159,16 +162,20 @@ struct wave_grad_state {
     int nseg = 0;       // segments: segment i covers steps i*C .. min((i+1)*C, nt) - 1
     int held = -1;      // segment whose levels' Laplacians the store holds
     bool has_src = false;
-    // checkpoints (two fields each; none with a single segment, which is
-    // never recomputed), then the store: lap a^c .. lap a^{c+C-1} of a segment
+    // one allocation: checkpoints (two fields each; none with a single
+    // segment, which is never recomputed), the store (lap a^c .. lap
+    // a^{c+C-1} of a segment), and the run's source values [nt]
     void *slab = nullptr;
     size_t slab_bytes = 0;
-    float *src = nullptr;  // the run's source values [nt]
-    int src_cap = 0;
+    float *src = nullptr;
+    // one allocation: the adjoint fields, the FP64 sum, and one more value
+    // (the source term)
+    void *work = nullptr;
     void *phi[2] = {nullptr, nullptr};
-    double *acc = nullptr;      // FP64 sum, then one more value: the source term
+    double *acc = nullptr;
     // receiver cells (distinct) by work-group of the adjoint's tiling, and,
-    // per cell, its receivers
+    // per cell, its receivers (one allocation)
+    void *cells = nullptr;
     int *cell_wg = nullptr;
     long long *cell_off = nullptr;
     int *cell_start = nullptr, *cell_rec = nullptr;
@@ -199,7 +206,9 @@ struct wave_ctx {
     float *traces = nullptr;
     int32_t trace_cap = 0;
     Coefs coefs{};
-    // device tables
+    // device tables: those that last (one allocation) and those of the
+    // launch configuration (another)
+    void *tables = nullptr, *rec_tables = nullptr;
     float *gx = nullptr, *gy = nullptr, *gz = nullptr;
     long long *rec_off_all = nullptr;  // receiver offsets in receiver order (naive sampling)
     int *rec_start = nullptr;
@@ -545,12 +554,42 @@ void free_dev(T *&p)
     }
 }
 
+// Several tables uploaded as one device allocation: an allocation, a copy
+// and a free each cost 10-100 us, more than the smallest shots' work.
+struct Upload {
+    std::vector<char> host;
+    template <class T>
+    size_t add(const T *p, size_t n)
+    {
+        const size_t at = host.size();
+        host.resize(at + size_t(round_up(int64_t(std::max<size_t>(n, 1) * sizeof(T)), 256)), 0);
+        if (n)
+            std::memcpy(host.data() + at, p, n * sizeof(T));
+        return at;
+    }
+    int send(void **dev) const
+    {
+        if (hipMalloc(dev, host.size()) != hipSuccess) {
+            *dev = nullptr;
+            (void)hipGetLastError();
+            return WAVE_ENOMEM;
+        }
+        return hipMemcpy(*dev, host.data(), host.size(), hipMemcpyHostToDevice) == hipSuccess ? WAVE_OK : WAVE_EHIP;
+    }
+};
+
+template <class T>
+T *table_at(void *base, size_t at)
+{
+    return reinterpret_cast<T *>(static_cast<char *>(base) + at);
+}
+
 // Per-work-group receiver lists for the tiled kernels.
 int build_receiver_tables(wave_ctx *c)
 {
-    free_dev(c->rec_start);
-    free_dev(c->rec_off);
-    free_dev(c->rec_idx);
+    free_dev(c->rec_tables);
+    c->rec_start = c->rec_idx = nullptr;
+    c->rec_off = nullptr;
     if (c->v_used == kNaive)
         return WAVE_OK;
     const Variant &V = kVariants[c->v_used];
@@ -571,12 +610,15 @@ int build_receiver_tables(wave_ctx *c)
         idx[slot] = r;
         off[slot] = elem_offset(c->lay, c->rec[3 * r], c->rec[3 * r + 1], c->rec[3 * r + 2]);
     }
-    HIP_TRY(c, hipMalloc(&c->rec_start, sizeof(int) * start.size()));
-    HIP_TRY(c, hipMalloc(&c->rec_off, sizeof(long long) * off.size()));
-    HIP_TRY(c, hipMalloc(&c->rec_idx, sizeof(int) * idx.size()));
-    HIP_TRY(c, hipMemcpy(c->rec_start, start.data(), sizeof(int) * start.size(), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(c->rec_off, off.data(), sizeof(long long) * off.size(), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(c->rec_idx, idx.data(), sizeof(int) * idx.size(), hipMemcpyHostToDevice));
+    Upload up;
+    const size_t at_off = up.add(off.data(), off.size()), at_start = up.add(start.data(), start.size()),
+                 at_idx = up.add(idx.data(), idx.size());
+    const int rc = up.send(&c->rec_tables);
+    if (rc != WAVE_OK)
+        return fail(c, WAVE_EHIP, "the receiver tables could not be uploaded");
+    c->rec_off = table_at<long long>(c->rec_tables, at_off);
+    c->rec_start = table_at<int>(c->rec_tables, at_start);
+    c->rec_idx = table_at<int>(c->rec_tables, at_idx);
     return WAVE_OK;
 }
 
@@ -707,14 +749,8 @@ int check_trace_room(wave_ctx *c, int64_t nsteps)
 void free_grad(wave_grad_state &g)
 {
     free_dev(g.slab);
-    free_dev(g.src);
-    free_dev(g.phi[0]);
-    free_dev(g.phi[1]);
-    free_dev(g.acc);
-    free_dev(g.cell_wg);
-    free_dev(g.cell_off);
-    free_dev(g.cell_start);
-    free_dev(g.cell_rec);
+    free_dev(g.work);
+    free_dev(g.cells);
     g = wave_grad_state();
 }
 
@@ -733,16 +769,16 @@ void free_device(wave_ctx *c)
 {
     drop_run_graph(c);
     free_grad(c->g);
-    free_dev(c->gx);
-    free_dev(c->gy);
-    free_dev(c->gz);
-    free_dev(c->rec_off_all);
-    free_dev(c->rec_start);
-    free_dev(c->rec_off);
-    free_dev(c->rec_idx);
-    free_dev(c->ring);
+    free_dev(c->tables);
+    free_dev(c->rec_tables);
     free_dev(c->k16);
     free_dev(c->dbuf);
+}
+
+// blocks of 64 x 4 threads for the kernels that go over the interior's rows
+dim3 row_blocks(int ny, int nz)
+{
+    return dim3((unsigned)std::min<long long>(((long long)ny * nz + 3) / 4, 2048));
 }
 
 int launch_convert(hipStream_t s, int src_kind, int dst_kind, const void *src, void *dst, int nx, int ny,
@@ -751,8 +787,7 @@ int launch_convert(hipStream_t s, int src_kind, int dst_kind, const void *src, v
 {
     src_kind = base_kind(src_kind);
     dst_kind = base_kind(dst_kind);
-    const long long n = (long long)nx * ny * nz;
-    const dim3 g((unsigned)std::min<long long>((n + 255) / 256, 8192)), b(256);
+    const dim3 g = row_blocks(ny, nz), b(64, 4);
     const int spx = int(sl.pitch_x), sx0 = int(sl.x_offset), dpx = int(dl.pitch_x),
               dx0 = int(dl.x_offset);
     const long long sp = sl.plane, dp = dl.plane;
@@ -917,10 +952,7 @@ int build_receiver_cells(wave_ctx *c, const Geo &geo)
     if (g.ncells >= 0 && g.cell_v == geo.v && g.cell_zc == geo.zc)
         return WAVE_OK;
     g.ncells = -1;
-    free_dev(g.cell_wg);
-    free_dev(g.cell_off);
-    free_dev(g.cell_start);
-    free_dev(g.cell_rec);
+    free_dev(g.cells);
     const Variant &V = kVariants[geo.v];
     const int tx = 4 * V.txv, tyr = V.ty * V.ry;
     struct Rec {
@@ -952,16 +984,15 @@ int build_receiver_cells(wave_ctx *c, const Geo &geo)
     for (int i = 0; i < geo.nwg; ++i)
         wg[i + 1] += wg[i];
     const int ncells = int(off.size());
-    off.resize(std::max<size_t>(off.size(), 1));
-    idx.resize(std::max<size_t>(idx.size(), 1));
-    HIP_TRY(c, hipMalloc(&g.cell_wg, sizeof(int) * wg.size()));
-    HIP_TRY(c, hipMalloc(&g.cell_off, sizeof(long long) * off.size()));
-    HIP_TRY(c, hipMalloc(&g.cell_start, sizeof(int) * start.size()));
-    HIP_TRY(c, hipMalloc(&g.cell_rec, sizeof(int) * idx.size()));
-    HIP_TRY(c, hipMemcpy(g.cell_wg, wg.data(), sizeof(int) * wg.size(), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(g.cell_off, off.data(), sizeof(long long) * off.size(), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(g.cell_start, start.data(), sizeof(int) * start.size(), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(g.cell_rec, idx.data(), sizeof(int) * idx.size(), hipMemcpyHostToDevice));
+    Upload up;
+    const size_t at_off = up.add(off.data(), off.size()), at_wg = up.add(wg.data(), wg.size()),
+                 at_start = up.add(start.data(), start.size()), at_rec = up.add(idx.data(), idx.size());
+    if (up.send(&g.cells) != WAVE_OK)
+        return fail(c, WAVE_EHIP, "the receiver cells could not be uploaded");
+    g.cell_off = table_at<long long>(g.cells, at_off);
+    g.cell_wg = table_at<int>(g.cells, at_wg);
+    g.cell_start = table_at<int>(g.cells, at_start);
+    g.cell_rec = table_at<int>(g.cells, at_rec);
     g.ncells = ncells;
     g.cell_v = geo.v;
     g.cell_zc = geo.zc;
@@ -1525,53 +1556,44 @@ int wave_init(wave_ctx **out, const wave_params_t *p, const void *k, void *u_cur
         }
     }
 
-    // sponge profiles
-    std::vector<float> g;
-    float **dst[3] = {&c->gx, &c->gy, &c->gz};
-    const int n3[3] = {p->nx, p->ny, p->nz};
-    for (int a = 0; a < 3; ++a) {
-        sponge_profile(n3[a], p->sponge_width, p->sponge_alpha, g);
-        if (hipMalloc(dst[a], sizeof(float) * g.size()) != hipSuccess)
-            return bail(WAVE_ENOMEM);
-        if (hipMemcpy(*dst[a], g.data(), sizeof(float) * g.size(), hipMemcpyHostToDevice) != hipSuccess)
-            return bail(WAVE_EHIP);
-    }
-    // receiver offsets in receiver order
+    // sponge profiles, receiver offsets in receiver order and the scale history
     {
-        std::vector<long long> off(std::max(nrec, 1));
+        Upload up;
+        size_t at[5];
+        std::vector<float> g;
+        const int n3[3] = {p->nx, p->ny, p->nz};
+        for (int a = 0; a < 3; ++a) {
+            sponge_profile(n3[a], p->sponge_width, p->sponge_alpha, g);
+            at[a] = up.add(g.data(), g.size());
+        }
+        std::vector<long long> off(nrec);
         for (int r = 0; r < nrec; ++r)
             off[r] = elem_offset(lay, c->rec[3 * r], c->rec[3 * r + 1], c->rec[3 * r + 2]);
-        if (hipMalloc(&c->rec_off_all, sizeof(long long) * off.size()) != hipSuccess)
-            return bail(WAVE_ENOMEM);
-        if (hipMemcpy(c->rec_off_all, off.data(), sizeof(long long) * off.size(), hipMemcpyHostToDevice) != hipSuccess)
-            return bail(WAVE_EHIP);
+        at[3] = up.add(off.data(), off.size());
+        const std::vector<int> zeros(kRingInts, 0);
+        at[4] = up.add(zeros.data(), zeros.size());
+        const int rc = up.send(&c->tables);
+        if (rc != WAVE_OK)
+            return bail(rc);
+        c->gx = table_at<float>(c->tables, at[0]);
+        c->gy = table_at<float>(c->tables, at[1]);
+        c->gz = table_at<float>(c->tables, at[2]);
+        c->rec_off_all = table_at<long long>(c->tables, at[3]);
+        c->ring = table_at<int>(c->tables, at[4]);
     }
-    if (hipMalloc(&c->ring, kRingInts * sizeof(int)) != hipSuccess)
-        return bail(WAVE_ENOMEM);
-    if (hipMemsetAsync(c->ring, 0, kRingInts * sizeof(int), c->stream) != hipSuccess)
-        return bail(WAVE_EHIP);
     plan_launch(c);
     if (build_receiver_tables(c) != WAVE_OK)
         return bail(WAVE_EHIP);
 
     // stability: max(k) * symbol_max * sum 1/h^2 <= 4 (k is FP32 in the FP32 layout)
-    unsigned *d = nullptr;
-    unsigned init[3] = {0u, 0x7f800000u, 0u}, res[3];
-    if (hipMalloc(&d, sizeof(init)) != hipSuccess)
-        return bail(WAVE_ENOMEM);
-    bool ok = hipMemcpyAsync(d, init, sizeof(init), hipMemcpyHostToDevice, c->stream) == hipSuccess;
-    if (ok) {
-        hipLaunchKernelGGL(k_range, dim3(1024), dim3(256), 0, c->stream, (const float *)k, p->nx,
-                           p->ny, p->nz, int(lay32.pitch_x), int(lay32.x_offset),
-                           (long long)lay32.plane, d);
-        ok = hipGetLastError() == hipSuccess &&
-             hipMemcpyAsync(res, d, sizeof(res), hipMemcpyDeviceToHost, c->stream) == hipSuccess &&
-             hipStreamSynchronize(c->stream) == hipSuccess;
-    }
-    (void)hipFree(d);
-    if (!ok)
+    unsigned *d = reinterpret_cast<unsigned *>(c->ring + kRingCounters), res[2];
+    hipLaunchKernelGGL(k_range, row_blocks(p->ny, p->nz), dim3(64, 4), 0, c->stream, (const float *)k, p->nx, p->ny,
+                       p->nz, int(lay32.pitch_x), int(lay32.x_offset), (long long)lay32.plane, d);
+    if (hipGetLastError() != hipSuccess ||
+        hipMemcpyAsync(res, d, sizeof(res), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+        hipStreamSynchronize(c->stream) != hipSuccess)
         return bail(WAVE_EHIP);
-    if (res[2])
+    if (res[1])
         return bail(WAVE_EINVAL);
     float kmax;
     std::memcpy(&kmax, &res[0], sizeof(float));
@@ -1831,7 +1853,8 @@ int wave_forward_checkpointed(wave_ctx *ctx, int32_t nt, const float *src_dev, i
     wave_grad_state &g = ctx->g;
     const int nseg = (nt + C - 1) / C;
     const size_t lb = level_bytes(ctx);
-    const size_t need = checkpoints(nseg) * lb + (size_t)C * lap_bytes(ctx);
+    const size_t levels = checkpoints(nseg) * lb + (size_t)C * lap_bytes(ctx);
+    const size_t need = levels + sizeof(float) * (src_dev ? (size_t)nt : 0);
     g.nt = 0;  // invalid until the run is enqueued
     if (need > g.slab_bytes) {
         free_dev(g.slab);
@@ -1844,12 +1867,7 @@ int wave_forward_checkpointed(wave_ctx *ctx, int32_t nt, const float *src_dev, i
         g.slab_bytes = need;
     }
     if (src_dev) {
-        if (nt > g.src_cap) {
-            free_dev(g.src);
-            g.src_cap = 0;
-            HIP_TRY(ctx, hipMalloc(&g.src, sizeof(float) * (size_t)nt));
-            g.src_cap = nt;
-        }
+        g.src = reinterpret_cast<float *>(static_cast<char *>(g.slab) + levels);
         HIP_TRY(ctx, hipMemcpyAsync(g.src, src_dev, sizeof(float) * (size_t)nt,
                                     hipMemcpyDeviceToDevice, ctx->stream));
     }
@@ -1897,12 +1915,15 @@ int adjoint_run(wave_ctx *ctx, const float *trace_grad_dev, bool src_term)
         return rc;
     const size_t lb = level_bytes(ctx);
     const size_t cells = (size_t)ctx->lap_plane * ctx->p.nz;
-    for (int i = 0; i < 2; ++i)
-        if (!g.phi[i]) {
-            HIP_TRY(ctx, hipMalloc(&g.phi[i], lb));
+    if (!g.work) {
+        if (hipMalloc(&g.work, 2 * lb + (cells + 1) * sizeof(double)) != hipSuccess) {
+            (void)hipGetLastError();
+            g.work = nullptr;
+            return fail(ctx, WAVE_EHIP, "cannot allocate the adjoint fields and the FP64 sum");
         }
-    if (!g.acc) {
-        HIP_TRY(ctx, hipMalloc(&g.acc, (cells + 1) * sizeof(double)));
+        g.phi[0] = g.work;
+        g.phi[1] = static_cast<char *>(g.work) + lb;
+        g.acc = reinterpret_cast<double *>(static_cast<char *>(g.work) + 2 * lb);
     }
     double *src_sum = g.acc + cells;
     if (g.held != g.nseg - 1) {
@@ -1910,8 +1931,7 @@ int adjoint_run(wave_ctx *ctx, const float *trace_grad_dev, bool src_term)
         if ((rc = recompute_segment(ctx, g.nseg - 1, g.phi)) != WAVE_OK)
             return rc;
     }
-    HIP_TRY(ctx, hipMemsetAsync(g.phi[0], 0, lb, ctx->stream));
-    HIP_TRY(ctx, hipMemsetAsync(g.phi[1], 0, lb, ctx->stream));
+    HIP_TRY(ctx, hipMemsetAsync(g.work, 0, 2 * lb, ctx->stream));
     HIP_TRY(ctx, hipMemsetAsync(src_sum, 0, sizeof(double), ctx->stream));
     src_term = src_term && g.has_src && ctx->src[0] >= 0;
 
@@ -2052,34 +2072,37 @@ int wave_velocity_to_k(const float *v_dev, int64_t n, double dt, float *k_dev, v
     return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_EHIP;
 }
 
-int wave_check(wave_ctx *ctx, int64_t *field_nonfinite, int64_t *trace_nonfinite)
+namespace {
+
+// wave_check with the two counters at d (device, cleared here)
+int count_nonfinite_into(wave_ctx *ctx, int *d, int64_t *field_nonfinite, int64_t *trace_nonfinite)
 {
-    if (!ctx)
-        return WAVE_EINVAL;
-    int *d = nullptr;
     int h[2] = {0, 0};
-    HIP_TRY(ctx, hipMalloc(&d, 2 * sizeof(int)));
-    const long long cells = (long long)ctx->p.nx * ctx->p.ny * ctx->p.nz;
     const long long nt = (ctx->traces && ctx->nrec > 0) ? std::min<long long>(ctx->step, ctx->trace_cap) : 0;
-    bool ok = hipMemsetAsync(d, 0, 2 * sizeof(int), ctx->stream) == hipSuccess;
-    if (ok) {
-        const dim3 g((unsigned)std::min<long long>((std::max(cells, nt * ctx->nrec) + 255) / 256, 4096));
-        hipLaunchKernelGGL(count_nonfinite, g, dim3(256), 0, ctx->stream, (const void *)ctx->cur,
-                           ctx->p.dtype, ctx->p.nx, ctx->p.ny, ctx->p.nz, int(ctx->lay.pitch_x),
-                           int(ctx->lay.x_offset), (long long)ctx->lay.plane, (const float *)ctx->traces,
-                           nt * ctx->nrec, d);
-        ok = hipGetLastError() == hipSuccess &&
-             hipMemcpyAsync(h, d, sizeof(h), hipMemcpyDeviceToHost, ctx->stream) == hipSuccess &&
-             hipStreamSynchronize(ctx->stream) == hipSuccess;
-    }
-    (void)hipFree(d);
-    if (!ok)
-        return fail(ctx, WAVE_EHIP, "wave_check failed");
+    hipLaunchKernelGGL(zero_ints, dim3(1), dim3(64), 0, ctx->stream, d, 2ll);
+    const dim3 rows = row_blocks(ctx->p.ny, ctx->p.nz);
+    const dim3 g(std::max(rows.x, (unsigned)std::min<long long>((nt * ctx->nrec + 1023) / 1024, 2048)));
+    hipLaunchKernelGGL(count_nonfinite, g, dim3(64, 4), 0, ctx->stream, (const void *)ctx->cur, ctx->p.dtype,
+                       ctx->p.nx, ctx->p.ny, ctx->p.nz, int(ctx->lay.pitch_x), int(ctx->lay.x_offset),
+                       (long long)ctx->lay.plane, (const float *)ctx->traces, nt * ctx->nrec, d);
+    if (hipGetLastError() != hipSuccess ||
+        hipMemcpyAsync(h, d, sizeof(h), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+        hipStreamSynchronize(ctx->stream) != hipSuccess)
+        return fail(ctx, WAVE_EHIP, "the check failed");
     if (field_nonfinite)
         *field_nonfinite = h[0];
     if (trace_nonfinite)
         *trace_nonfinite = h[1];
     return WAVE_OK;
+}
+
+}  // namespace
+
+int wave_check(wave_ctx *ctx, int64_t *field_nonfinite, int64_t *trace_nonfinite)
+{
+    if (!ctx)
+        return WAVE_EINVAL;
+    return count_nonfinite_into(ctx, ctx->ring + kRingCounters, field_nonfinite, trace_nonfinite);
 }
 
 int wave_set_adjoint_fusion(wave_ctx *ctx, int32_t on)
@@ -2115,25 +2138,7 @@ int wave_check_noalloc(wave_ctx *ctx, int64_t *field_nonfinite, int64_t *trace_n
     int *d = nullptr;
     if (scratch_for(ctx->device, &d) != WAVE_OK)
         return fail(ctx, WAVE_EHIP, "wave_check_noalloc: the scratch array's address is not available");
-    int h[kCounters] = {0, 0};
-    const long long cells = (long long)ctx->p.nx * ctx->p.ny * ctx->p.nz;
-    const long long nt = (ctx->traces && ctx->nrec > 0) ? std::min<long long>(ctx->step, ctx->trace_cap) : 0;
-    // the array keeps the last call's counts: clear them with a kernel first
-    hipLaunchKernelGGL(zero_ints, dim3(1), dim3(256), 0, ctx->stream, d, (long long)kCounters);
-    const dim3 g((unsigned)std::min<long long>((std::max(cells, nt * ctx->nrec) + 255) / 256, 4096));
-    hipLaunchKernelGGL(count_nonfinite, g, dim3(256), 0, ctx->stream, (const void *)ctx->cur, ctx->p.dtype,
-                       ctx->p.nx, ctx->p.ny, ctx->p.nz, int(ctx->lay.pitch_x), int(ctx->lay.x_offset),
-                       (long long)ctx->lay.plane, (const float *)ctx->traces, nt * ctx->nrec, d);
-    const bool ok = hipGetLastError() == hipSuccess &&
-                    hipMemcpyAsync(h, d, sizeof(h), hipMemcpyDeviceToHost, ctx->stream) == hipSuccess &&
-                    hipStreamSynchronize(ctx->stream) == hipSuccess;
-    if (!ok)
-        return fail(ctx, WAVE_EHIP, "wave_check_noalloc failed");
-    if (field_nonfinite)
-        *field_nonfinite = h[0];
-    if (trace_nonfinite)
-        *trace_nonfinite = h[1];
-    return WAVE_OK;
+    return count_nonfinite_into(ctx, d, field_nonfinite, trace_nonfinite);
 }
 
 int wave_misfit(const float *traces_dev, const float *observed_dev, int64_t n, float *residual_dev,

@@ -43,6 +43,7 @@
 #include <utility>
 
 #include "wave_dev.h"
+#include "wave_kernels.h"
 
 namespace wavek {
 
@@ -1287,21 +1288,38 @@ __global__ __launch_bounds__(256) void convert_interior(const void *__restrict__
                                                         long long dplane, float scale,
                                                         const int *exps, int slot)
 {
-    const long long n = (long long)nx * ny * nz;
     const float sc = exps ? ldexpf(1.f, exps[slot]) : scale;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(i % nx);
-        const int y = (int)((i / nx) % ny);
-        const int z = (int)(i / ((long long)nx * ny));
+    for_interior_groups(nx, ny, nz, [&](int z, int y, int x, int n) {
         const long long si = (long long)(z + kGhost) * splane + (long long)(y + kGhost) * spx + sx0 + x;
         const long long di = (long long)(z + kGhost) * dplane + (long long)(y + kGhost) * dpx + dx0 + x;
-        const float v = read_elem<SRC>(src, si, 1.f);
-        if constexpr (DST == WAVE_F32)
-            static_cast<float *>(dst)[di] = v * sc;
+        // the whole group is read (right-ghost cells past nx are allocated)
+        // and, unless it is a ragged one, written whole
+        Raw4<SRC> in;
+        if constexpr (SRC == WAVE_F32)
+            in = *reinterpret_cast<const u4raw *>(static_cast<const float *>(src) + si);
         else
-            static_cast<unsigned short *>(dst)[di] = (unsigned short)Store<DST>::enc(v * sc);
-    }
+            in = *reinterpret_cast<const u2raw *>(static_cast<const unsigned short *>(src) + si);
+        f4 v = decode4<SRC>(in);
+        for (int e = 0; e < 4; ++e)
+            v.v[e] *= sc;
+        if constexpr (DST == WAVE_F32) {
+            float *d = static_cast<float *>(dst) + di;
+            if (n == 4)
+                *reinterpret_cast<f4 *>(d) = v;
+            else
+                for (int e = 0; e < n; ++e)
+                    d[e] = v.v[e];
+        } else {
+            unsigned short *d = static_cast<unsigned short *>(dst) + di;
+            if (n == 4)
+                *reinterpret_cast<ushort4 *>(d) =
+                    ushort4{(unsigned short)Store<DST>::enc(v.v[0]), (unsigned short)Store<DST>::enc(v.v[1]),
+                            (unsigned short)Store<DST>::enc(v.v[2]), (unsigned short)Store<DST>::enc(v.v[3])};
+            else
+                for (int e = 0; e < n; ++e)
+                    d[e] = (unsigned short)Store<DST>::enc(v.v[e]);
+        }
+    });
 }
 
 }  // namespace wavek
