@@ -291,6 +291,7 @@ void sponge_profile(int n, int width, double alpha, std::vector<float> &g)
 // step; 128^3: 7.3 against 25.9).
 constexpr int kAutoVariant = 10;     // t256x8_r1 (FP32)
 constexpr int kAutoNarrowVariant = 6;  // t128x16_r1 (FP32 when 256-wide tiles would idle lanes)
+constexpr int kTallVariant = 12;     // t128x32_r2 (FP32 streamed from HBM, one round)
 constexpr int kAuto16Variant = 4;    // t128x16_r2 (FP16 / BF16, two levels, the largest grids)
 constexpr int kSmallVariant = 2;     // t64x16_r1 for grids of fewer than 2^22 cells
 constexpr int kTargetWorkgroupsSmall = 512;
@@ -353,7 +354,8 @@ long long round_workgroups(int kind, int v)
 // 16 grids from 112 x 304 x 240 to 600 x 1200 x 200, every chunk count
 // measured, with 128 x 16 tiles; the other large-grid plans it gives are
 // the ones measured best before it.
-int fill_rounds_chunk(long long tiles, int nz, int min_chunk, long long cap, double *score = nullptr)
+int fill_rounds_chunk(long long tiles, int nz, int min_chunk, long long cap, double *score = nullptr,
+                      bool one_round = false)
 {
     double best = -1.0;
     int zc = nz;
@@ -365,6 +367,8 @@ int fill_rounds_chunk(long long tiles, int nz, int min_chunk, long long cap, dou
             continue;  // the same chunk length as c - 1
         const long long nwg = tiles * ((nz + z - 1) / z);
         const long long rounds = (nwg + cap - 1) / cap;
+        if (one_round && rounds > 1)
+            break;
         const double eff = double(nwg) / double(rounds * cap) * std::pow(0.85, double(rounds - 1)) /
                            (1.0 + 2.0 / z);
         if (eff > best + 1e-12) {
@@ -396,6 +400,7 @@ double tile_fit(int nx, int ny, int tx, int tyr)
 struct Cand32 {
     int v;
     double weight;
+    bool one_round;  // only as a single round of work-groups
 };
 
 int plan32(int nx, int ny, int nz, const Cand32 *cand, int n, int *zc)
@@ -407,7 +412,8 @@ int plan32(int nx, int ny, int nz, const Cand32 *cand, int n, int *zc)
         const int tx = 4 * C.txv, tyr = C.ty * C.ry;
         const long long tiles = (long long)((nx + tx - 1) / tx) * ((ny + tyr - 1) / tyr);
         double eff = 0.0;
-        const int z = fill_rounds_chunk(tiles, nz, kMinChunk, round_workgroups(WAVE_F32, cand[i].v), &eff);
+        const int z = fill_rounds_chunk(tiles, nz, kMinChunk, round_workgroups(WAVE_F32, cand[i].v), &eff,
+                                        cand[i].one_round);
         eff *= tile_fit(nx, ny, tx, tyr) * cand[i].weight;
         if (eff > best * (1.0 + 1e-9)) {
             best = eff;
@@ -481,15 +487,27 @@ Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
     if (v == 0 && !large) {
         v = kSmallVariant;
     } else if (v == 0 && kind == WAVE_F32) {
-        // FP32: 128 x 16 or 256 x 8 tiles.  Where at least 95 % of a 256-wide
+        // 128 x 16 or 256 x 8 tiles.  Where at least 95 % of a 256-wide
         // tile's lanes lie in the grid the wide tiles get 2 %: on full tiles,
         // where both shapes score the same, they are 1.5-3 % faster (512^3:
         // 323 against 337 us; 256^3: 38.9 against 39.8).
+        // Fields streamed from HBM also try 128 x 32 tiles of two rows per
+        // thread, which need half the work-groups: where they make a single
+        // round of what takes the others more, or the same share of one with
+        // half the halo rows, they are 3-8 % faster (755x994x200: 444 -> 412
+        // us; 401x800x400: 408 -> 388; 512x700x300: 313 -> 291).  Within
+        // three fields of 4 GiB in all: beyond, the plan tests hold the wide
+        // tiles (755x994x1000: 2329 us, 2217 with these).
         const bool wide = double(nx) / (256.0 * ((nx + 255) / 256)) >= 0.95;
-        const Cand32 cand[] = {{kAutoNarrowVariant, 1.0}, {kAutoVariant, wide ? 1.02 : 1.0}};
+        wave_layout_t lay;
+        const bool tall = !fits_in_cache(nx, ny, nz) && wave_layout(nx, ny, nz, WAVE_F32, &lay) == WAVE_OK &&
+                          3 * lay.bytes <= (int64_t(1) << 32);
+        const Cand32 cand[] = {{kAutoNarrowVariant, 1.0, false},
+                               {kAutoVariant, wide ? 1.02 : 1.0, false},
+                               {kTallVariant, 1.02, true}};
         v = wide ? kAutoVariant : kAutoNarrowVariant;
         if (zc <= 0)
-            v = plan32(nx, ny, nz, cand, 2, &zc);
+            v = plan32(nx, ny, nz, cand, tall ? 3 : 2, &zc);
     } else if (v == 0) {
         // 16-bit.  Two levels on grids of 2^27 cells or more take 128 x 16
         // tiles of two rows in two work-groups per CU: BF16 512^3 187 us
@@ -840,7 +858,7 @@ Geo adjoint_geo(const wave_ctx *c)
     const wave_params_t &p = c->p;
     if ((long long)p.nx * p.ny * p.nz < (1ll << 22))
         return plan_geo(p.nx, p.ny, p.nz, WAVE_F32, kSmallVariant, 0);
-    const Cand32 cand[] = {{kAutoNarrowVariant, 1.0}, {kAutoVariant, 0.95}, {kSmallVariant, 0.94}};
+    const Cand32 cand[] = {{kAutoNarrowVariant, 1.0, false}, {kAutoVariant, 0.95, false}, {kSmallVariant, 0.94, false}};
     int zc = 0;
     const int v = plan32(p.nx, p.ny, p.nz, cand, 3, &zc);
     return plan_geo(p.nx, p.ny, p.nz, WAVE_F32, v, zc);
