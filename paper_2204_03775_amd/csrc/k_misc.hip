@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256) void grad_to_dense(const double *__restrict__ 
 __global__ void clear_counters(int *c)
 {
     if (threadIdx.x < 16)
-        c[threadIdx.x] = 0;
+        c[kTicketStride * threadIdx.x] = 0;
 }
 
 // Zero n ints (a kernel, not a memset, so that it can sit in a captured graph).

@@ -1043,7 +1043,7 @@ struct wave_batch {
         std::vector<int> shots;       // indices into ctx
         std::vector<ShotDesc> h_desc; // last uploaded descriptors
         ShotDesc *d_desc = nullptr;
-        int *d_items = nullptr;       // shot[items], lid[items], xcd_start[9], counters[16], run sync[4]
+        int *d_items = nullptr;       // counters, run sync[4], then shot[items], lid[items], xcd_start[9]
         BatchItems items{};
         int total = 0, grid = 0, threads = 0;
         // schedule 2: FlowShot table, xcd_shot[9], xcd_items[8], then the
@@ -1297,11 +1297,11 @@ int run_enqueue(wave_batch *b, int nsteps)
             cells += (long long)b->ctx[t]->p.nx * b->ctx[t]->p.ny * b->ctx[t]->p.nz;
         const double seconds = 2.0 + nsteps * (1e-4 + double(cells) * 1e-10);
         int *words = g.items.counters;
-        hipLaunchKernelGGL(zero_ints, dim3(1), dim3(256), 0, b->stream, words, (long long)(16 + kRunSyncInts));
+        hipLaunchKernelGGL(zero_ints, dim3(1), dim3(256), 0, b->stream, words, (long long)(kTicketInts + kRunSyncInts));
         RunSync rs;
-        rs.count = reinterpret_cast<unsigned *>(words + 16);
-        rs.gen = reinterpret_cast<unsigned *>(words + 17);
-        rs.abort = words + 18;
+        rs.count = reinterpret_cast<unsigned *>(words + kTicketInts);
+        rs.gen = reinterpret_cast<unsigned *>(words + kTicketInts + 1);
+        rs.abort = words + kTicketInts + 2;
         // a negative wait limit (a test hook) makes every barrier wait give up at once
         rs.timeout = b->wait_limit < 0 ? 0ull : (unsigned long long)(seconds * khz * 1000.0);
         rs.j0 = 0;
@@ -2271,11 +2271,10 @@ int wave_batch_create(wave_batch **out, wave_ctx *const *ctxs, int32_t nshots, v
             per_cu < 1)
             per_cu = 1;
         g.grid = int(round_up(std::min<long long>((long long)per_cu * cus, g.total), 8));
-        std::vector<int> blob;
+        std::vector<int> blob(kTicketInts + kRunSyncInts, 0);  // tickets [2][8], then the run's barrier words
         blob.insert(blob.end(), ishot.begin(), ishot.end());
         blob.insert(blob.end(), ilid.begin(), ilid.end());
         blob.insert(blob.end(), xs.begin(), xs.end());
-        blob.insert(blob.end(), 16 + kRunSyncInts, 0);  // tickets [2][8], then the run's barrier words
         g.h_desc.assign(g.shots.size(), ShotDesc{});
         std::memset(g.h_desc.data(), 0, sizeof(ShotDesc) * g.h_desc.size());
         if (hipMalloc(&g.d_desc, sizeof(ShotDesc) * g.shots.size()) != hipSuccess ||
@@ -2284,10 +2283,10 @@ int wave_batch_create(wave_batch **out, wave_ctx *const *ctxs, int32_t nshots, v
             delete b;
             return WAVE_ENOMEM;
         }
-        g.items.shot = g.d_items;
-        g.items.lid = g.d_items + g.total;
-        g.items.xcd_start = g.d_items + 2 * g.total;
-        g.items.counters = g.d_items + 2 * g.total + 9;
+        g.items.counters = g.d_items;
+        g.items.shot = g.d_items + kTicketInts + kRunSyncInts;
+        g.items.lid = g.items.shot + g.total;
+        g.items.xcd_start = g.items.lid + g.total;
         if (hipMemcpy(g.d_items, blob.data(), sizeof(int) * blob.size(), hipMemcpyHostToDevice) !=
                 hipSuccess ||
             hipMemcpy(g.d_desc, g.h_desc.data(), sizeof(ShotDesc) * g.h_desc.size(),
@@ -2537,7 +2536,7 @@ int wave_batch_sync(wave_batch *b)
     if (b->schedule == 3)
         for (const auto &g : b->groups) {
             int flag = 0;
-            if (hipMemcpy(&flag, g.items.counters + 18, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
+            if (hipMemcpy(&flag, g.items.counters + kTicketInts + 2, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
                 return bfail(b, WAVE_EHIP, "schedule 3 status could not be read");
             if (flag)
                 return bfail(b, WAVE_EHIP, "schedule 3: a barrier wait ran past its limit; the run's results are invalid");

@@ -119,13 +119,16 @@ struct ShotDesc {
     const float *src;  // source values of the run's steps, or NULL (then no source)
 };
 
+constexpr int kTicketStride = 32;                    // ints between two ticket counters (a 128-byte line)
+constexpr int kTicketInts = 2 * 8 * kTicketStride;
+
 // Work items of a batched step: (shot, tile and z-chunk of that shot),
 // split into 8 contiguous ranges of about equal work, one per XCD.
 struct BatchItems {
     const int *shot;       // [items] shot (index into the group's descriptors)
     const int *lid;        // [items] tile/chunk number within the shot
     const int *xcd_start;  // [9] item range of each XCD
-    int *counters;         // [2][8] tickets of the current and the next step
+    int *counters;         // [2][8] tickets of the current and the next step, kTicketStride apart
 };
 
 // Single-launch run of a batch (schedule 3): the grid barrier between steps
