@@ -332,7 +332,9 @@ int wave_batch_run(wave_batch *b, int32_t nsteps, const float *const *src_dev);
  *   schedule 1  every shot's steps launched with its own kernel
  *               configuration, the shots dealt, largest first, to the least
  *               loaded (in cells) of nstreams (1..16) streams of the library
- *               that fork from and join back to the batch stream; with
+ *               that fork from and join back to the batch stream (fewer are
+ *               used, but at least two, where the shots running at once would
+ *               not share the GPU's memory-side cache); with
  *               use_graph each stream's share of the run is captured as a
  *               graph of its own, replayed on that stream (so the streams
  *               run concurrently) while the shots' states, sources, trace
