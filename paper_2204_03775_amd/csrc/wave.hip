@@ -638,6 +638,24 @@ int build_receiver_tables(wave_ctx *c)
     return WAVE_OK;
 }
 
+// Launch geometry, with the multipliers that replace the tile numbers'
+// divisions (see div_by; exact for every work-group number, or 0).
+void set_geo(StepArgs &a, int ntx, int nty, int nchunks, int zc, int nwg)
+{
+    a.ntx = ntx;
+    a.nty = nty;
+    a.nchunks = nchunks;
+    a.zc = zc;
+    a.nwg = nwg;
+    auto multiplier = [&](int d) -> unsigned {
+        // d = 0: a kernel without tiles
+        return d > 0 && (unsigned long long)nwg * d <= (1ull << 32)
+                   ? 0xffffffffu / unsigned(d) : 0u;
+    };
+    a.mtx = multiplier(ntx);
+    a.mty = multiplier(nty);
+}
+
 StepArgs make_args(const wave_ctx *c)
 {
     StepArgs a;
@@ -655,11 +673,7 @@ StepArgs make_args(const wave_ctx *c)
     a.x0 = int(c->lay.x_offset);
     a.plane = c->lay.plane;
     a.nxq = (c->p.nx + 3) / 4;
-    a.ntx = c->ntx;
-    a.nty = c->nty;
-    a.nchunks = c->nchunks;
-    a.zc = c->zc_used;
-    a.nwg = c->nwg;
+    set_geo(a, c->ntx, c->nty, c->nchunks, c->zc_used, c->nwg);
     a.src_z = c->src[0];
     a.src_y = c->src[1];
     a.src_x = c->src[2];
@@ -878,11 +892,7 @@ int enqueue_adjoint(wave_ctx *c, const Geo &geo, const void *near, void *far, co
     a.aux = lap;
     a.dlt = lap_far;
     a.first = first ? 1 : 0;
-    a.ntx = geo.ntx;
-    a.nty = geo.nty;
-    a.nchunks = geo.nchunks;
-    a.zc = geo.zc;
-    a.nwg = geo.nwg;
+    set_geo(a, geo.ntx, geo.nty, geo.nchunks, geo.zc, geo.nwg);
     a.src_z = a.src_y = a.src_x = -1;
     a.src_ptr = nullptr;
     // the receiver cells take the receivers' place in the tables

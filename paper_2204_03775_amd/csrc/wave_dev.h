@@ -58,6 +58,7 @@ struct StepArgs {
     long long plane;    // elements per plane
     int nxq;            // ceil(nx / 4): 4-cell columns holding interior cells
     int ntx, nty, nchunks, zc, nwg;
+    unsigned mtx, mty;  // division multipliers of ntx, nty (see div_by)
     int src_z, src_y, src_x;  // src_z < 0: no source
     const float *src_ptr;     // device value of this step, or NULL
     float src_val;            // used when src_ptr is NULL

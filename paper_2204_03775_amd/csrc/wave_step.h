@@ -68,10 +68,11 @@ __device__ __forceinline__ float mul_rounded(float x, float g)
 // b % 8 share an XCD, not necessarily XCD b % 8); map block b to logical
 // work-group (b % 8) * (G / 8) + b / 8 so that each XCD gets a contiguous
 // run of neighbouring tiles whose halos share its L2.
-__device__ __forceinline__ int logical_wg()
+// (G, the grid, is the work-groups rounded up to a multiple of 8.)
+__device__ __forceinline__ int logical_wg(const StepArgs &a)
 {
     const int b = blockIdx.x;
-    const int per = gridDim.x >> 3;
+    const int per = (a.nwg + 7) >> 3;
     return (b & 7) * per + (b >> 3);
 }
 
@@ -376,6 +377,19 @@ __device__ __forceinline__ void fold_max(const StepArgs &a, int lid, float m)
     }
 }
 
+// n / d for the tile numbers: the high word of (n + 1) m with m =
+// floor((2^32 - 1) / d), exact for (n + 1) d <= 2^32 (the host sets m = 0
+// beyond), instead of a division's 30 instructions at the head of every launch.
+__device__ __forceinline__ int div_by(int n, int d, unsigned m)
+{
+    unsigned q = __umulhi((unsigned)n + 1u, m);
+    if (__builtin_expect(m == 0, 0)) {
+        keep_branch();
+        q = (unsigned)n / (unsigned)d;
+    }
+    return (int)q;
+}
+
 // Receiver epilogue: after the whole tile column is written, copy the
 // receivers this work-group owns (r0 .. r1 - 1 of its tables, looked up
 // before the march) into the trace row.  A thread's first table entries are
@@ -471,17 +485,16 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     constexpr int PKK = CACHED ? kKeep : kStream;
     __shared__ f4 lds[2][LH][LW];
 
-    const int tx = lid % a.ntx;
-    const int rest = lid / a.ntx;
-    const int ty = rest % a.nty;
-    const int ch = rest / a.nty;
+    const int rest = div_by(lid, a.ntx, a.mtx), tx = lid - rest * a.ntx;
+    const int ch = div_by(rest, a.nty, a.mty), ty = rest - ch * a.nty;
     const int z0 = ch * a.zc;
     const int z1 = min(z0 + a.zc, a.nz);
     // the chunk's planes in march order: march position l is plane zp(l)
     // (positions -4 .. -1 and len .. len + 3 are the chunk's z halo)
     const int len = z1 - z0;
     const bool down = a.zdown & 1;
-    auto zp = [&](int l) { return down ? z1 - 1 - l : z0 + l; };
+    const int zb = down ? z1 - 1 : z0, dz = down ? -1 : 1;
+    auto zp = [&](int l) { return zb + dz * l; };
 
     const int tid = threadIdx.x;
     const int lx = tid % TXV;
@@ -490,14 +503,6 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     const int y0 = ty * TYR;           // first row of the tile
     const int xq = xq0 + lx;           // this thread's 4-cell column
     const int x = 4 * xq;
-
-    Scales sc{1.f, 1.f, 1.f, 1.f, 0};
-    Folded fd{a.c, 2.f, 1.f, 1.f};
-    if constexpr (SCALED) {
-        sc = step_scales<KIND>(a);
-        publish_scale(a, sc, lid, tid);
-        fd = fold_scales(a.c, sc, a.k_scale);
-    }
 
     // Only 4-cell groups holding interior cells are read (the ragged last
     // group's right-ghost lanes with them); ghost rows, columns and planes
@@ -520,94 +525,28 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
         own_ld[r] = own_in[r];
     }
 
-    // halo items of this thread
+    // halo items of this thread: 8 rows of the tile's width above and below
+    // it, then the columns left and right (selects, no branches: a small
+    // grid's launch is as long as one wave's instructions)
+    auto halo_item = [](int i, int &hr, int &hc) {
+        const int band = i / TXV, j = i - 8 * TXV;
+        const bool rows = i < 8 * TXV;
+        hr = rows ? band - 4 + (band < 4 ? 0 : TYR) : j % TYR;
+        hc = rows ? i % TXV : j < TYR ? -1 : TXV;
+    };
     unsigned h_b[HPT];
     int h_lds[HPT];  // flat LDS index (row * LW + col), -1 when unused
 #pragma unroll
     for (int h = 0; h < HPT; ++h) {
-        const int i = tid + h * NT;
         int hr, hc;
-        if (i < 8 * TXV) {
-            const int band = i / TXV;
-            hr = band < 4 ? band - 4 : TYR + band - 4;
-            hc = i % TXV;
-        } else {
-            const int j = i - 8 * TXV;
-            hr = j % TYR;
-            hc = (j / TYR) ? TXV : -1;
-        }
-        const bool use = i < NH;
+        halo_item(tid + h * NT, hr, hc);
+        const bool use = tid + h * NT < NH;
         h_lds[h] = use ? (hr + 4) * LW + (hc + 1) : -1;
         const int gy = y0 + hr;
         const int gq = xq0 + hc;
-        const bool ok = use && gy >= 0 && gy < a.ny && gq >= 0 && gq < a.nxq;
-        h_b[h] = ok ? EB * unsigned((gy + kGhost) * a.px + a.x0 + 4 * gq) : kOff;
+        const bool ok = use & ((unsigned)gy < (unsigned)a.ny) & ((unsigned)gq < (unsigned)a.nxq);
+        h_b[h] = EB * unsigned((gy + kGhost) * a.px + a.x0 + 4 * gq) | (ok ? 0u : kOff);
     }
-    // adjoint: sponge factor g_x g_y of every cell this thread loads
-    // (cells outside the interior hold zeros; their factor is irrelevant)
-    f4 gh[ADJ ? HPT : 1];
-    if constexpr (ADJ) {
-#pragma unroll
-        for (int h = 0; h < HPT; ++h) {
-            const int i = tid + h * NT;
-            int hr, hc;
-            if (i < 8 * TXV) {
-                const int band = i / TXV;
-                hr = band < 4 ? band - 4 : TYR + band - 4;
-                hc = i % TXV;
-            } else {
-                const int j = i - 8 * TXV;
-                hr = j % TYR;
-                hc = (j / TYR) ? TXV : -1;
-            }
-            const int gy = y0 + hr;
-            const float fy = (gy >= 0 && gy < a.ny) ? a.gy[gy] : 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int gxi = 4 * (xq0 + hc) + e;
-                gh[h].v[e] = (gxi >= 0 && gxi < a.nx) ? a.gx[gxi] * fy : 0.f;
-            }
-        }
-    }
-
-    // sponge factors that do not change along z
-    f4 gxv = {{1.f, 1.f, 1.f, 1.f}};
-    if (col_interior) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            gxv.v[e] = (x + e < a.nx) ? a.gx[x + e] : 1.f;
-    }
-    float gyv[RY];
-#pragma unroll
-    for (int r = 0; r < RY; ++r)
-        gyv[r] = row_int[r] ? a.gy[row[r]] : 1.f;
-    f4 gown[ADJ ? RY : 1];  // adjoint: g_x g_y of the own cells
-    if constexpr (ADJ) {
-#pragma unroll
-        for (int r = 0; r < RY; ++r)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                gown[r].v[e] = gxv.v[e] * gyv[r];
-    }
-
-    // source ownership (the value is read once, before the march)
-    int src_r = -1, src_e = 0;
-    if (a.src_z >= z0 && a.src_z < z1 && (a.src_x >> 2) == xq) {
-#pragma unroll
-        for (int r = 0; r < RY; ++r)
-            if (row[r] == a.src_y)
-                src_r = r;
-        src_e = a.src_x & 3;
-    }
-    const float sval = src_r >= 0 ? src_value(a) * sc.out_inv : 0.f;
-
-    // this work-group's receivers (adjoint: receiver cells)
-    int rec0 = 0, rec1 = 0;
-    if (a.trace_row) {
-        rec0 = a.rec_start[lid];
-        rec1 = a.rec_start[lid + 1];
-    }
-
     const long long pbytes = a.plane * (long long)EB;
     const __amdgpu_buffer_rsrc_t gz_r = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(a.gz), (short)0, a.nz * (int)sizeof(float), kRsrcWord3);
@@ -617,22 +556,29 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     auto gz_at = [&](int z) {  // g_z, zero outside the interior (reads nothing there)
         return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gz_r, 4u * unsigned(z), 0, 0));
     };
+    // The prologue issues every load of the first plane before anything that
+    // waits for one (scales, sponge factors, the source's value), and gets
+    // there in few instructions: a small grid's launch is the serial chain of
+    // one wave, half of it instructions and half memory latency, and the first
+    // load used to be the 290th instruction (now the 140th).  64^3 under graph
+    // replay 3.59 -> 3.43 us a step, 37 x 21 x 19 3.39 -> 3.18; FP16 at 64^3
+    // 5.39 -> 5.22, FP16 u and step change at 128^3 9.08 -> 8.87; 256^3 and up
+    // as before.
     f4 q[QS][RY];
+    float gzi[ADJ ? 8 : 1];
+    const long long zstep = down ? -pbytes : pbytes;
+    const long long zfirst = (long long)(zp(0) + kGhost) * pbytes;
+    const char *pq = reinterpret_cast<const char *>(a.cur) + zfirst - 4 * zstep;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int zi = zp(i - 4);
-        const __amdgpu_buffer_rsrc_t rc = stencil_plane_rsrc(a.cur, pbytes, zi, a.nz);
+        const __amdgpu_buffer_rsrc_t rc = rsrc_at(pq, pbytes, (unsigned)zi < (unsigned)a.nz);
+        pq += zstep;
 #pragma unroll
         for (int r = 0; r < RY; ++r)
             q[i][r] = load4<KIND, PK>(rc, own_ld[r], 1.f);
-        if constexpr (ADJ) {
-            const float gzi = gz_at(zi);
-#pragma unroll
-            for (int r = 0; r < RY; ++r)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    q[i][r].v[e] = mul_rounded(q[i][r].v[e], gown[r].v[e] * gzi);
-        }
+        if constexpr (ADJ)
+            gzi[i] = gz_at(zi);
     }
 
     // values of the next plane, loaded one plane ahead into the set of the
@@ -664,9 +610,6 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     // 32.0 -> 30.4); the FP32 kernels, which have issue slots to spare, run
     // 0.5-1 % faster with absolute ones (256^3 39.5 against 39.8 us).
     constexpr bool INC = SCALED;
-    const long long zstep = down ? -pbytes : pbytes;
-    const long long zfirst = (long long)(zp(0) + kGhost) * pbytes;
-    const char *pq = reinterpret_cast<const char *>(a.cur) + zfirst + 4 * zstep;
     const char *ph = reinterpret_cast<const char *>(a.cur) + zfirst;
     const char *pp = reinterpret_cast<const char *>(UV ? a.dlt : a.nxt) + zfirst;
     const char *pk = reinterpret_cast<const char *>(a.k) + zfirst;
@@ -723,6 +666,81 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
         }
     };
     prefetch(0, 8, 0);
+
+    // this work-group's receivers (adjoint: receiver cells)
+    int rec0 = 0, rec1 = 0;
+    if (a.trace_row) {
+        rec0 = a.rec_start[lid];
+        rec1 = a.rec_start[lid + 1];
+    }
+
+    // sponge factors that do not change along z (masked cells' are never used)
+    const __amdgpu_buffer_rsrc_t gx_r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(a.gx), (short)0, 4 * a.nxq * (int)sizeof(float), kRsrcWord3);
+    const __amdgpu_buffer_rsrc_t gy_r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(a.gy), (short)0, a.ny * (int)sizeof(float), kRsrcWord3);
+    auto gx_at = [&](int x4) {  // four factors (x4 a multiple of 4; the table is padded to whole groups)
+        return decode4<WAVE_F32>(__builtin_amdgcn_raw_buffer_load_b128(gx_r, 4u * unsigned(x4), 0, 0));
+    };
+    auto gy_at = [&](int y) {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gy_r, 4u * unsigned(y), 0, 0));
+    };
+    const f4 gxv = gx_at(x);
+    float gyv[RY];
+#pragma unroll
+    for (int r = 0; r < RY; ++r)
+        gyv[r] = gy_at(row[r]);
+    // adjoint: g_x g_y of every cell this thread loads (zero outside the
+    // grid, whose cells hold zeros)
+    f4 gh[ADJ ? HPT : 1];
+    f4 gown[ADJ ? RY : 1];
+    if constexpr (ADJ) {
+        f4 fx[HPT];
+        float fy[HPT];
+#pragma unroll
+        for (int h = 0; h < HPT; ++h) {
+            int hr, hc;
+            halo_item(tid + h * NT, hr, hc);
+            fx[h] = gx_at(4 * (xq0 + hc));
+            fy[h] = gy_at(y0 + hr);
+        }
+#pragma unroll
+        for (int h = 0; h < HPT; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                gh[h].v[e] = fx[h].v[e] * fy[h];
+#pragma unroll
+        for (int r = 0; r < RY; ++r)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                gown[r].v[e] = gxv.v[e] * gyv[r];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int r = 0; r < RY; ++r)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    q[i][r].v[e] = mul_rounded(q[i][r].v[e], gown[r].v[e] * gzi[i]);
+    }
+
+    Scales sc{1.f, 1.f, 1.f, 1.f, 0};
+    Folded fd{a.c, 2.f, 1.f, 1.f};
+    if constexpr (SCALED) {
+        sc = step_scales<KIND>(a);
+        publish_scale(a, sc, lid, tid);
+        fd = fold_scales(a.c, sc, a.k_scale);
+    }
+
+    // source ownership (the value is read once, before the march)
+    int src_r = -1, src_e = 0;
+    if (a.src_z >= z0 && a.src_z < z1 && (a.src_x >> 2) == xq) {
+#pragma unroll
+        for (int r = 0; r < RY; ++r)
+            if (row[r] == a.src_y)
+                src_r = r;
+        src_e = a.src_x & 3;
+    }
+    const float sval = src_r >= 0 ? src_value(a) * sc.out_inv : 0.f;
 
     float tmax = 0.f;  // max |stored u^{n+1}| written by this thread (16-bit storage)
     const Coefs c = fd.c;
@@ -924,7 +942,7 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
 template <int KIND, int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void step_tiled(StepArgs a)
 {
-    const int lid = logical_wg();
+    const int lid = logical_wg(a);
     if (lid >= a.nwg)
         return;
     tile_step<KIND, TXV, TY, RY>(a, lid);
@@ -937,7 +955,7 @@ __global__ __launch_bounds__(TXV *TY) void step_tiled(StepArgs a)
 template <int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void step_tiled_cached(StepArgs a)
 {
-    const int lid = logical_wg();
+    const int lid = logical_wg(a);
     if (lid >= a.nwg)
         return;
     tile_step<WAVE_F32, TXV, TY, RY, kFwd, false, true>(a, lid);
@@ -954,7 +972,7 @@ __global__ __launch_bounds__(TXV *TY) void step_tiled_cached(StepArgs a)
 template <bool CACHED, int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void step_tiled_lap(StepArgs a)
 {
-    const int lid = logical_wg();
+    const int lid = logical_wg(a);
     if (lid >= a.nwg)
         return;
     tile_step<WAVE_F32, TXV, TY, RY, kLap, false, CACHED>(a, lid);
@@ -963,7 +981,7 @@ __global__ __launch_bounds__(TXV *TY) void step_tiled_lap(StepArgs a)
 template <int MODE, int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void adjoint_tiled(StepArgs a)
 {
-    const int lid = logical_wg();
+    const int lid = logical_wg(a);
     if (lid >= a.nwg)
         return;
     tile_step<WAVE_F32, TXV, TY, RY, MODE>(a, lid);
