@@ -132,6 +132,10 @@ struct Store<WAVE_BF16_UV> : Store<WAVE_BF16> {
     static constexpr bool uv = true;
 };
 
+// Vector arithmetic (first) or LDS accesses stay on their side of this point.
+__device__ __forceinline__ void in_order() { __builtin_amdgcn_sched_barrier(0x3f4); }
+__device__ __forceinline__ void reads_in_order() { __builtin_amdgcn_sched_barrier(0x7f); }
+
 // Raw buffer access.  A buffer resource covers one plane of one field; any
 // byte offset at or past its size reads as zero and drops stores, which is
 // how out-of-range tile cells are masked without branches.
@@ -460,7 +464,11 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
 {
     constexpr int NT = TXV * TY;
     constexpr int TYR = TY * RY;             // tile rows
-    constexpr int LW = TXV + 2;              // float4 per LDS row: one halo float4 each side
+    // float4 per LDS row: one halo float4 each side.  A wave of a 16-wide tile
+    // reads four rows at once, without bank conflicts only if they lie a
+    // multiple of 16 float4 apart (rows of 18: 42 % of the LDS cycles were
+    // conflicts; rows of 32: 11 %)
+    constexpr int LW = TXV == 16 ? 32 : TXV + 2;
     constexpr int LH = TYR + 8;              // LDS rows: 4 halo rows each side
     constexpr int NH = 8 * TXV + 2 * TYR;    // halo float4 per plane
     constexpr int HPT = (NH + NT - 1) / NT;  // halo float4 per thread
@@ -782,14 +790,26 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
             __syncthreads();
 
             // y taps: LDS rows ly*RY - 4 .. ly*RY + RY + 3 of this column,
-            // own rows straight from the queue
-            f4 ycol[RY + 8];
+            // own rows straight from the queue; x taps: the groups left and
+            // right of the own rows'.  16-bit storage reads them in the order
+            // of their use.
+            f4 ycol[RY + 8], xlr[RY][2];
+            auto x_taps = [&](int r) {
+                xlr[r][0] = L[(4 + ly * RY + r) * LW + lx];
+                xlr[r][1] = L[(4 + ly * RY + r) * LW + lx + 2];
+            };
 #pragma unroll
-            for (int j = 0; j < RY + 8; ++j) {
-                if (j >= 4 && j < 4 + RY)
-                    ycol[j] = q[(s + 4) % QS][j - 4];
-                else
-                    ycol[j] = L[(ly * RY + j) * LW + lx + 1];
+            for (int r = 0; r < RY; ++r) {
+                ycol[4 + r] = q[(s + 4) % QS][r];
+                if constexpr (SCALED)
+                    x_taps(r);
+            }
+#pragma unroll
+            for (int m = 1; m <= 4; ++m) {
+                if constexpr (SCALED)
+                    reads_in_order();
+                ycol[4 - m] = L[(ly * RY + 4 - m) * LW + lx + 1];
+                ycol[3 + RY + m] = L[(ly * RY + 3 + RY + m) * LW + lx + 1];
             }
             const __amdgpu_buffer_rsrc_t ro = INC ? rsrc_at(po, pbytes) : plane_rsrc(a.out, pbytes, z);
             const __amdgpu_buffer_rsrc_t rdl = rsrc_at(UV ? pd : po, pbytes);
@@ -799,10 +819,9 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                 pd += zstep;
 #pragma unroll
             for (int r = 0; r < RY; ++r) {
-                const f4 pvd = decode4<KIND>(pv[cur_set][r]);
-                const f4 kvd = decode4<KIND>(kv[cur_set][r]);
-                const f4 xl = L[(4 + ly * RY + r) * LW + lx];
-                const f4 xr = L[(4 + ly * RY + r) * LW + lx + 2];
+                if constexpr (!SCALED)
+                    x_taps(r);
+                const f4 xl = xlr[r][0], xr = xlr[r][1];
                 const f4 ctr = q[(s + 4) % QS][r];
                 float xs[12];
 #pragma unroll
@@ -811,21 +830,61 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                     xs[4 + e] = ctr.v[e];
                     xs[8 + e] = xr.v[e];
                 }
+                // 16-bit storage: the z sums, which need no LDS, while its
+                // reads are on the way, then sums and FMAs four cells at a
+                // time: an instruction that needs the one before it waits
+                // 8 cycles instead of 4, and left to itself the compiler
+                // finishes one cell after the other.  (us a step, before ->
+                // now with the LDS rows above: 320x288x272 FP16 44.1 -> 41.3,
+                // 200x190x180 FP16 21.2 -> 18.8, 512^3 205 -> 201; u and change
+                // 128^3 8.82 -> 8.50, 256^3 36.0 -> 33.9, 512^3 239 -> 235.
+                // FP32 steps, which wait for bandwidth, gain nothing and pay
+                // 20 registers: 755x994x200 407 -> 410.)
+                float lapc[4];
+                if constexpr (SCALED) {
+                    float zs[4][4], ts[4];
+#pragma unroll
+                    for (int m = 1; m <= 4; ++m)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            zs[m - 1][e] = q[(s + 4 + m) % QS][r].v[e] + q[(s + 4 - m + QS) % QS][r].v[e];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        lapc[e] = c.ctr * ctr.v[e];
+#pragma unroll
+                    for (int m = 1; m <= 4; ++m) {
+                        in_order();
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            ts[e] = xs[4 + e + m] + xs[4 + e - m];
+                        in_order();
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            lapc[e] = fmaf(c.cx[m - 1], ts[e], lapc[e]);
+                        in_order();
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            ts[e] = ycol[4 + r + m].v[e] + ycol[4 + r - m].v[e];
+                        in_order();
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            lapc[e] = fmaf(c.cy[m - 1], ts[e], lapc[e]);
+                        in_order();
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            lapc[e] = fmaf(c.cz[m - 1], zs[m - 1][e], lapc[e]);
+                    }
+                    in_order();
+                }
+                const f4 pvd = decode4<KIND>(pv[cur_set][r]);
+                const f4 kvd = decode4<KIND>(kv[cur_set][r]);
                 f4 out, lapv;
                 float img[FUS ? 2 : 1][4];  // imaging terms: of phi^m (centre) and of phi^{m+1}
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float lap;
                     if constexpr (SCALED) {
-                        lap = c.ctr * ctr.v[e];
-#pragma unroll
-                        for (int m = 1; m <= 4; ++m) {
-                            lap = fmaf(c.cx[m - 1], xs[4 + e + m] + xs[4 + e - m], lap);
-                            lap = fmaf(c.cy[m - 1], ycol[4 + r + m].v[e] + ycol[4 + r - m].v[e], lap);
-                            lap = fmaf(c.cz[m - 1],
-                                       q[(s + 4 + m) % QS][r].v[e] + q[(s + 4 - m + QS) % QS][r].v[e],
-                                       lap);
-                        }
+                        lap = lapc[e];
                     } else {
                         const float u2 = 2.f * ctr.v[e];
                         lap = 0.f;
