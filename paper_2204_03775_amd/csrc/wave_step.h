@@ -610,7 +610,7 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
     auto sum_at = [&](int z, int r) {
         return reinterpret_cast<dv2 *>(a.grad + (long long)z * a.lplane + own_lap[r] / 4);
     };
-    float gzv[2], gzq[2];  // g_z of the plane and (adjoint) of the queue plane four positions on
+    float gzv[2], gzq[2];  // FP32: g_z of the plane, and (adjoint) of the queue plane four positions on
     // Addresses of the planes being loaded and written.  16-bit storage
     // advances them by one plane per iteration, two scalar adds per field in
     // place of the multiplies of an absolute address (83 -> 54 scalar
@@ -662,7 +662,8 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                 }
             }
         }
-        gzv[set] = gz_at(z);
+        if constexpr (!SCALED)
+            gzv[set] = gz_at(z);
         if constexpr (ADJ)
             gzq[set] = gz_at(zp(l + 4));
         if constexpr (INC) {
@@ -674,6 +675,19 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
         }
     };
     prefetch(0, 8, 0);
+    // 16-bit storage: g_z of the aligned 64 march positions around l, one a
+    // lane, and of the next 64.  A load a plane was the sixth part of the
+    // loads of steps that keep the address units busy half the time (us a
+    // step: 320x288x272 FP16 41.2 -> 40.4, 512^3 200.7 -> 193.4; u and change
+    // 401x397x300 BF16 111.8 -> 108.7, 256^3 FP16 33.8 -> 33.2).  FP32 steps
+    // keep it: 512^3 323 -> 322, but 256^3 42.0 -> 42.2, 64^3 3.78 -> 3.84.
+    const int lane = tid & 63;
+    float gzw = 1.f, gzn = 1.f;
+    if constexpr (SCALED) {
+        gzw = gz_at(zp(lane));
+        if (len > 64)
+            gzn = gz_at(zp(64 + lane));
+    }
 
     // this work-group's receivers (adjoint: receiver cells)
     int rec0 = 0, rec1 = 0;
@@ -760,6 +774,13 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                 return false;
             const int z = zp(l);
             constexpr int cur_set = s & 1;
+            if constexpr (SCALED) {
+                if (l > 0 && (l & 63) == 0) {
+                    keep_branch();
+                    gzw = gzn;
+                    gzn = gz_at(zp(l + 64 + lane));
+                }
+            }
             prefetch(l + 1, (s + 9) % QS, cur_set ^ 1);
             if constexpr (ADJ) {
                 // psi = G phi: the plane that just entered the queue (four positions on)
@@ -811,6 +832,8 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                 ycol[4 - m] = L[(ly * RY + 4 - m) * LW + lx + 1];
                 ycol[3 + RY + m] = L[(ly * RY + 3 + RY + m) * LW + lx + 1];
             }
+            const float gz = SCALED ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(gzw), l & 63))
+                                    : gzv[cur_set];
             const __amdgpu_buffer_rsrc_t ro = INC ? rsrc_at(po, pbytes) : plane_rsrc(a.out, pbytes, z);
             const __amdgpu_buffer_rsrc_t rdl = rsrc_at(UV ? pd : po, pbytes);
             if constexpr (INC)
@@ -899,7 +922,7 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
                                        lap);
                         }
                     }
-                    const float g = gxv.v[e] * gyv[r] * gzv[cur_set];
+                    const float g = gxv.v[e] * gyv[r] * gz;
                     if constexpr (LAP)
                         lapv.v[e] = lap;
                     if constexpr (ADJ) {
