@@ -1,0 +1,140 @@
+"""Remainders of kernels and launch rules: chunks longer than a window of 64
+planes, large ragged gradient plans, batches of shots larger than the
+memory-side cache, and grids and lengths around the row and block sizes of the
+utility kernels.  Everything but the misfit's sum is compared bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2204_03775_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def make(wave, p, dtype="f32", config=(0, 0)):
+    prop = wave.Propagator(p.nx, p.ny, p.nz, p.h, p.k32(), src=p.src, rec=p.rec,
+                           sponge_width=p.sponge_width, sponge_alpha=p.sponge_alpha, dtype=dtype)
+    prop.configure(*config)
+    prop.record(p.nt)
+    return prop
+
+
+def src_of(p):
+    return torch.tensor(p.s, dtype=torch.float32, device="cuda")
+
+
+def state(prop):
+    cur, prev, _ = prop.fields()
+    return [prop.padded(b).view(torch.int16).cpu().numpy().copy() for b in (cur, prev)] + \
+        [prop.traces.cpu().numpy()]
+
+
+# 16-bit steps hold the z sponge factors of 64 planes at a time: chunks that
+# end at, before and after a multiple of 64, and several windows, marched up
+# and down (consecutive steps alternate) through a sponge as deep as the grid
+@pytest.mark.parametrize("zc", [63, 64, 65, 128, 129, 197])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f16uv", "bf16uv"])
+def test_long_chunks_16bit(wave_mod, zc, dtype):
+    p = inputs.random_problem(21, 18, 197, 5, seed=zc, sponge_width=98, sponge_alpha=0.01, nrec=12)
+    out = []
+    for config in (("t64x16_r1", zc), ("t128x32_r2", zc), (1, 0)):
+        print(f"case: {dtype} {config}", flush=True)
+        prop = make(wave_mod, p, dtype, config)
+        prop.run(p.nt, src_of(p))
+        prop.sync()
+        out.append(state(prop))
+        prop.close()
+    for tiled in out[:2]:
+        for a, b in zip(tiled, out[2]):
+            assert np.array_equal(a, b)
+
+
+# gradient plans of grids of 2^22 cells and more, no multiple of any tile:
+# every level kept and checkpointed runs with odd and even step counts (the
+# imaging terms go in pairs), against a tile shape given by the caller
+@pytest.mark.parametrize("shape", [(163, 161, 160), (515, 91, 93), (131, 260, 131)])
+@pytest.mark.parametrize("nt,every", [(6, 0), (7, 0), (7, 3), (8, 3)])
+def test_gradient_plan_matches_given_tiling(wave_mod, shape, nt, every):
+    p = inputs.random_problem(*shape, nt, seed=shape[0] + nt, sponge_width=5, nrec=40)
+    tg = torch.tensor(np.random.default_rng(nt).standard_normal((nt, len(p.rec))), dtype=torch.float32,
+                      device="cuda")
+    out = []
+    for config in ((0, 0), ("t128x8_r1", 24)):
+        print(f"case: gradient {shape} nt {nt} every {every} {config}", flush=True)
+        prop = make(wave_mod, p, "f32", config)
+        for b, seed in zip(prop.fields()[:2], (1, 2)):  # a wave field everywhere from the first level on
+            gen = torch.Generator(device="cuda").manual_seed(seed)
+            prop.interior(b)[:] = torch.randn((p.nz, p.ny, p.nx), device="cuda", generator=gen)
+        prop.forward_checkpointed(nt, src_of(p), every)
+        g = prop.adjoint(tg)
+        prop.sync()
+        out.append(g.cpu().numpy())
+        prop.close()
+    assert np.array_equal(out[0], out[1])
+    assert np.abs(out[0]).max() > 0
+
+
+# shots whose fields alone exceed the memory-side cache run on two streams,
+# whatever number is asked for
+@pytest.mark.parametrize("nstreams,graph", [(1, False), (3, False), (3, True)])
+def test_streams_of_shots_larger_than_the_cache(wave_mod, nstreams, graph):
+    shots = [inputs.random_problem(276 + i, 264, 260 - i, 4, seed=i, sponge_width=4, nrec=9) for i in range(3)]
+    ref = []
+    for p in shots:
+        prop = make(wave_mod, p)
+        prop.run(p.nt, src_of(p))
+        prop.sync()
+        ref.append(prop.traces.cpu().numpy())
+        prop.close()
+    props = [make(wave_mod, p) for p in shots]
+    batch = wave_mod.Batch(props, use_graph=graph)
+    batch.set_schedule(1, nstreams)
+    srcs = [src_of(p) for p in shots]
+    for rep in range(2):
+        print(f"case: {nstreams} streams, graph={graph}, run {rep}", flush=True)
+        for prop in props:
+            prop.reset()
+        batch.run(shots[0].nt, srcs)
+        batch.sync()
+        torch.cuda.synchronize()
+        for prop, r in zip(props, ref):
+            assert np.array_equal(prop.traces.cpu().numpy(), r)
+    batch.close()
+    for prop in props:
+        prop.close()
+
+
+# set-up scan, export and non-finite count: groups of four cells, 64 groups to
+# a row of threads, four rows to a block
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 5, 2), (64, 4, 3), (67, 5, 3), (259, 9, 2), (513, 3, 5)])
+def test_utility_kernels_reach_the_last_cell(wave_mod, shape):
+    nx, ny, nz = shape
+    p = inputs.random_problem(nx, ny, nz, 2, seed=nx, nrec=1)
+    print(f"case: utilities {shape}", flush=True)
+    prop = make(wave_mod, p)
+    cur, prev, _ = prop.fields()
+    vals = torch.randn((nz, ny, nx), device="cuda")
+    prop.interior(cur)[:] = vals
+    assert torch.equal(prop.export(0), vals)
+    prop.interior(cur)[-1, -1, -1] = float("nan")
+    prop.interior(cur)[0, 0, 0] = float("inf")
+    assert prop.check()[0] == (2 if nx * ny * nz > 1 else 1)
+    prop.close()
+    for bad in (float("nan"), -1.0, float("inf")):
+        k = p.k32().copy()
+        k.reshape(-1)[-1] = bad
+        with pytest.raises(wave_mod.WaveError):
+            wave_mod.Propagator(nx, ny, nz, p.h, k, src=p.src, rec=p.rec).close()
+
+
+# the sum of n squares in FP64, in any order: relative error below (n + 1) 2^-53 a side
+@pytest.mark.parametrize("n", [7, 2047, 2048, 2049, 8191, 8193, 65537])
+def test_misfit_lengths(wave_mod, n):
+    rng = np.random.default_rng(n)
+    a = torch.tensor(rng.standard_normal(n), dtype=torch.float32, device="cuda")
+    b = torch.tensor(rng.standard_normal(n), dtype=torch.float32, device="cuda")
+    J, r = wave_mod.misfit(a, b)
+    torch.cuda.synchronize()
+    assert torch.equal(r, a - b)
+    ref = 0.5 * np.sum((a.cpu().numpy().astype(np.float64) - b.cpu().numpy()) ** 2)
+    assert abs(J.item() - ref) <= (n + 2) * 2.0 ** -52 * ref
