@@ -29,7 +29,7 @@ int probe_read3_write1(const float *a, const float *b, const float *c, float *d,
 
 /* o[i] = a[i] + b[i] + c[i] + d[i]; g[i] += o[i] in FP64 (g: n doubles):
  * four FP32 reads, an FP64 read and write and an FP32 write per element
- * (36 bytes), the access mix of one fused adjoint-and-imaging update. */
+ * (36 bytes), the access mix of an adjoint step adding one imaging term. */
 int probe_adjoint_mix(const float *a, const float *b, const float *c, const float *d, double *g,
                       float *o, int64_t n, void *stream);
 
@@ -75,7 +75,8 @@ int probe_step_stream(const float *a, float *b, const float *k, int nx, int ny, 
 int probe_step_stream16(const void *u, void *p, void *o, const void *k, int nx, int ny, int nz, int64_t pitch,
                         int64_t x0, int zc, int ty, int ry, int down, void *stream);
 
-/* The fused adjoint step's access pattern without its arithmetic, on FP32
+/* The access pattern of an adjoint step that adds one imaging term and makes
+ * the forward level's Laplacian itself, without its arithmetic, on FP32
  * fields in the layout above (c, a, p, k) and an FP64 accumulator g with the
  * same layout in 8-byte cells (16-byte aligned pointers): c and a read four
  * planes ahead of the march (default policy), p and k at the plane

@@ -83,9 +83,10 @@ struct alignas(16) d2 {
 };
 
 // o = a + b + c + d, g += o (FP64): four FP32 reads, an FP64 read and write
-// and an FP32 write per element, 36 bytes: the access mix of the fused
-// adjoint step (phi^{m+1}, phi^{m+2}, k and the forward level in; phi^m and
-// the FP64 gradient accumulator out).
+// and an FP32 write per element, 36 bytes: the access mix of an adjoint step
+// that adds one imaging term (phi^{m+1}, phi^{m+2}, k and a forward field
+// in; phi^m and the FP64 sum out).  The library's step adds two terms every
+// other launch, 28 bytes a launch on average.
 __global__ __launch_bounds__(kThreads) void adjmix_k(const f4 *__restrict__ a, const f4 *__restrict__ b,
                                                      const f4 *__restrict__ c, const f4 *__restrict__ d,
                                                      d2 *__restrict__ g, f4 *__restrict__ o, long long n4)
@@ -313,7 +314,8 @@ __global__ __launch_bounds__(32 * TY) void step_stream16_k(const void *u, void *
     }
 }
 
-// The fused adjoint step's access pattern without its arithmetic: FP32
+// The access pattern of an adjoint step that makes the Laplacian of a
+// forward level itself, without its arithmetic: FP32
 // fields c (phi^{m+1}) and a (the forward level) read four planes ahead of
 // the march with the default policy, p (phi^{m+2}) and k at the plane
 // non-temporally, the FP64 accumulator g (8-byte cells, same layout) read
