@@ -437,7 +437,8 @@ int plan32(int nx, int ny, int nz, const Cand32 *cand, int n, int *zc)
 // with every tile shape and chunk count timed: the choice averages 1.015
 // times the fastest plan; one tile shape with chunks of at least 32 planes
 // averaged 1.64 (two levels) and 1.73 (u and change) times it (203x181x157
-// FP16: 38.3 -> 17.6 us a step; 320x288x272: 60.3 -> 44.6).
+// FP16: 38.3 -> 17.6 us a step; 320x288x272: 60.3 -> 44.6, and 40.3 with the
+// plane loop as it is now, under which the choices are still the best found).
 struct Plan16 {
     int v;
     double tau, alpha;
