@@ -1802,7 +1802,11 @@ int wave_reset(wave_ctx *ctx)
     ctx->cur = ctx->buf0;
     ctx->prev = ctx->buf1;
     ctx->step = 0;
-    HIP_TRY(ctx, hipMemsetAsync(ctx->ring, 0, kRingInts * sizeof(int), ctx->stream));
+    // FP32 steps have no scale history, and wave_check clears its counters
+    // itself.  The clear was one of the 33 launches of a run of 30 single
+    // steps at 37 x 21 x 19: 118.5 -> 116.8 us.
+    if (ctx->p.dtype != WAVE_F32)
+        HIP_TRY(ctx, hipMemsetAsync(ctx->ring, 0, kRingInts * sizeof(int), ctx->stream));
     if (ctx->dbuf)
         HIP_TRY(ctx, hipMemsetAsync(ctx->dbuf, 0, ctx->lay.bytes, ctx->stream));
     return WAVE_OK;
