@@ -194,8 +194,8 @@ __global__ __launch_bounds__(256) void k_range(const float *__restrict__ k, int 
                 continue;  // right-ghost cells: ignored
             if (!(v.v[e] >= 0.f) || !(v.v[e] < INFINITY))
                 bad = 1u;
-            else
-                mx = max(mx, __float_as_uint(v.v[e]));
+            else  // -0.0 passes the test above, and as bits it exceeds every positive value
+                mx = max(mx, __float_as_uint(fabsf(v.v[e])));
         }
     });
     const int t = threadIdx.y * blockDim.x + threadIdx.x;

@@ -110,3 +110,27 @@ def test_binding_refuses_short_or_wrong_arrays(wave_mod, prob):
     b.close()
     assert wave_mod.wave_fields(prop.ctx)[2] == 0  # nothing ran
     prop.close()
+
+
+# -0.0 is a k of zero, whatever its sign bit: it takes no part in the largest
+# value the stability check and the 16-bit scale of k are made from
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16uv"])
+def test_negative_zero_k_does_not_hide_the_largest(wave_mod, dtype):
+    nx, ny, nz, h = 21, 10, 9, (10.0, 10.0, 10.0)
+    print(f"case: -0.0 in k, {dtype}", flush=True)
+    k = np.full((nz, ny, nx), 1e4, dtype=np.float32)  # the leapfrog limit is 20.5
+    k[3, 4, 5] = -0.0
+    with pytest.raises(wave_mod.WaveError) as e:
+        wave_mod.Propagator(nx, ny, nz, h, k, src=(4, 5, 6), dtype=dtype).close()
+    assert e.value.code == wave_mod.WAVE_EUNSTABLE
+    # a stable k gives the same run with either zero (16-bit: the same scale of k)
+    out = []
+    for zero in (0.0, -0.0):
+        k = np.full((nz, ny, nx), 7.0, dtype=np.float32)
+        k[3, 4, 5] = zero
+        prop = wave_mod.Propagator(nx, ny, nz, h, k, src=(4, 5, 6), dtype=dtype)
+        prop.run(12, torch.linspace(1.0, -1.0, 12, device="cuda"))
+        out.append(prop.export(0).cpu().numpy())
+        prop.close()
+    assert np.abs(out[0]).max() > 0
+    assert np.array_equal(*out)
