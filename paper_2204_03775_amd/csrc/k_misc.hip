@@ -239,8 +239,8 @@ __global__ __launch_bounds__(256) void count_nonfinite(const void *__restrict__ 
                 bad_f += e < cells && (b[e] & m) == m;  // all-ones exponent: infinity or NaN
         }
     });
-    const long long t = ((long long)blockIdx.x * blockDim.y + threadIdx.y) * blockDim.x + threadIdx.x;
-    for (long long i = t; i < n; i += (long long)gridDim.x * blockDim.x * blockDim.y)
+    const long long block = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+    for (long long i = block * 256 + threadIdx.y * blockDim.x + threadIdx.x; i < n; i += 256ll * gridDim.x * gridDim.y)
         bad_t += !isfinite(traces[i]);
     if (bad_f)
         atomicAdd(&out[0], bad_f);

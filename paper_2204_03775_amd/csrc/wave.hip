@@ -806,11 +806,30 @@ void free_device(wave_ctx *c)
     free_dev(c->dbuf);
 }
 
-// blocks of 64 x 4 threads for the kernels that go over the interior's rows
-dim3 row_blocks(int ny, int nz)
-{
-    return dim3((unsigned)std::min<long long>(((long long)ny * nz + 3) / 4, 2048));
-}
+// Launch of the kernels that go over the interior's rows (for_interior_groups):
+// blocks of 256 threads, as many along a row as it has groups of four cells
+// (at most a wave), the rest over rows; where the rows are too few to fill the
+// GPU, several blocks share one.  With 64 x 4 threads and blocks over rows
+// alone, grids of short rows left most lanes idle and grids of few rows most
+// CUs: a call of wave_export with its output's clear took 427 us at
+// 262144 x 2 x 2 (now 31), 380 at 3 x 2000 x 700 (155) and 537 at
+// 8 x 1500 x 1500 (285).
+struct RowBlocks {
+    dim3 grid, block;
+    RowBlocks(int nx, int ny, int nz)
+    {
+        constexpr long long most = 2048;  // eight blocks a CU
+        const int groups = (nx + 3) / 4;
+        int bx = 1;
+        while (bx < groups && bx < 64)
+            bx *= 2;
+        const int by = 256 / bx;
+        const long long over_rows = std::min(((long long)ny * nz + by - 1) / by, most);
+        const long long along = std::min<long long>((groups + bx - 1) / bx, most / over_rows);
+        block = dim3(bx, by);
+        grid = dim3((unsigned)over_rows, (unsigned)along);
+    }
+};
 
 int launch_convert(hipStream_t s, int src_kind, int dst_kind, const void *src, void *dst, int nx, int ny,
                    int nz, const wave_layout_t &sl, const wave_layout_t &dl, float scale,
@@ -818,12 +837,12 @@ int launch_convert(hipStream_t s, int src_kind, int dst_kind, const void *src, v
 {
     src_kind = base_kind(src_kind);
     dst_kind = base_kind(dst_kind);
-    const dim3 g = row_blocks(ny, nz), b(64, 4);
+    const RowBlocks rows(nx, ny, nz);
     const int spx = int(sl.pitch_x), sx0 = int(sl.x_offset), dpx = int(dl.pitch_x),
               dx0 = int(dl.x_offset);
     const long long sp = sl.plane, dp = dl.plane;
 #define CONV(S, D)                                                                                 \
-    hipLaunchKernelGGL((convert_interior<S, D>), g, b, 0, s, src, dst, nx, ny, nz, spx, sx0, sp, dpx, \
+    hipLaunchKernelGGL((convert_interior<S, D>), rows.grid, rows.block, 0, s, src, dst, nx, ny, nz, spx, sx0, sp, dpx, \
                        dx0, dp, scale, exps, slot)
     if (src_kind == WAVE_F32 && dst_kind == WAVE_F16)
         CONV(WAVE_F32, WAVE_F16);
@@ -1622,8 +1641,8 @@ int wave_init(wave_ctx **out, const wave_params_t *p, const void *k, void *u_cur
 
     // stability: max(k) * symbol_max * sum 1/h^2 <= 4 (k is FP32 in the FP32 layout)
     unsigned *d = reinterpret_cast<unsigned *>(c->ring + kRingCounters), res[2];
-    hipLaunchKernelGGL(k_range, row_blocks(p->ny, p->nz), dim3(64, 4), 0, c->stream, (const float *)k, p->nx, p->ny,
-                       p->nz, int(lay32.pitch_x), int(lay32.x_offset), (long long)lay32.plane, d);
+    const RowBlocks rows(p->nx, p->ny, p->nz);
+    hipLaunchKernelGGL(k_range, rows.grid, rows.block, 0, c->stream, (const float *)k, p->nx, p->ny, p->nz, int(lay32.pitch_x), int(lay32.x_offset), (long long)lay32.plane, d);
     if (hipGetLastError() != hipSuccess ||
         hipMemcpyAsync(res, d, sizeof(res), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)
@@ -2119,9 +2138,9 @@ int count_nonfinite_into(wave_ctx *ctx, int *d, int64_t *field_nonfinite, int64_
     int h[2] = {0, 0};
     const long long nt = (ctx->traces && ctx->nrec > 0) ? std::min<long long>(ctx->step, ctx->trace_cap) : 0;
     hipLaunchKernelGGL(zero_ints, dim3(1), dim3(64), 0, ctx->stream, d, 2ll);
-    const dim3 rows = row_blocks(ctx->p.ny, ctx->p.nz);
-    const dim3 g(std::max(rows.x, (unsigned)std::min<long long>((nt * ctx->nrec + 1023) / 1024, 2048)));
-    hipLaunchKernelGGL(count_nonfinite, g, dim3(64, 4), 0, ctx->stream, (const void *)ctx->cur, ctx->p.dtype,
+    RowBlocks rows(ctx->p.nx, ctx->p.ny, ctx->p.nz);
+    rows.grid.x = std::max(rows.grid.x, (unsigned)std::min<long long>((nt * ctx->nrec + 1023) / 1024, 2048));
+    hipLaunchKernelGGL(count_nonfinite, rows.grid, rows.block, 0, ctx->stream, (const void *)ctx->cur, ctx->p.dtype,
                        ctx->p.nx, ctx->p.ny, ctx->p.nz, int(ctx->lay.pitch_x), int(ctx->lay.x_offset),
                        (long long)ctx->lay.plane, (const float *)ctx->traces, nt * ctx->nrec, d);
     if (hipGetLastError() != hipSuccess ||

@@ -9,16 +9,17 @@ namespace wavek {
 
 // Calls f(z, y, x, n) for the interior's groups of up to four cells of a row
 // (n = 4, fewer in a ragged last group), x a multiple of 4: groups start on
-// 16 (FP32) or 8 (16-bit) bytes.  Blocks of 64 x 4 threads take four rows at
-// a time, so a row's place costs one 32-bit division however long it is (a
-// 64-bit division of a cell number per cell costs more than moving the cell).
+// 16 (FP32) or 8 (16-bit) bytes.  Blocks take blockDim.y rows at a time, so a
+// row's place costs one 32-bit division however long it is (a 64-bit division
+// of a cell number per cell costs more than moving the cell); gridDim.y blocks
+// share a row (see RowBlocks).
 template <class F>
 __device__ __forceinline__ void for_interior_groups(int nx, int ny, int nz, F &&f)
 {
     const unsigned rows = (unsigned)ny * (unsigned)nz;
     for (unsigned row = blockIdx.x * blockDim.y + threadIdx.y; row < rows; row += gridDim.x * blockDim.y) {
         const int z = (int)(row / (unsigned)ny), y = (int)(row - (unsigned)z * (unsigned)ny);
-        for (int x = 4 * threadIdx.x; x < nx; x += 4 * blockDim.x)
+        for (int x = 4 * (blockIdx.y * blockDim.x + threadIdx.x); x < nx; x += 4 * blockDim.x * gridDim.y)
             f(z, y, x, min(4, nx - x));
     }
 }

@@ -1424,9 +1424,10 @@ __global__ __launch_bounds__(256) void convert_interior(const void *__restrict__
             float *d = static_cast<float *>(dst) + di;
             if (n == 4)
                 *reinterpret_cast<f4 *>(d) = v;
-            else
-                for (int e = 0; e < n; ++e)
-                    d[e] = v.v[e];
+            if (n & 2)
+                *reinterpret_cast<float2 *>(d) = float2{v.v[0], v.v[1]};
+            if (n & 1)
+                d[n & 2] = (n & 2) ? v.v[2] : v.v[0];
         } else {
             unsigned short *d = static_cast<unsigned short *>(dst) + di;
             if (n == 4)
@@ -1434,8 +1435,10 @@ __global__ __launch_bounds__(256) void convert_interior(const void *__restrict__
                     ushort4{(unsigned short)Store<DST>::enc(v.v[0]), (unsigned short)Store<DST>::enc(v.v[1]),
                             (unsigned short)Store<DST>::enc(v.v[2]), (unsigned short)Store<DST>::enc(v.v[3])};
             else
-                for (int e = 0; e < n; ++e)
-                    d[e] = (unsigned short)Store<DST>::enc(v.v[e]);
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (e < n)
+                        d[e] = (unsigned short)Store<DST>::enc(v.v[e]);
         }
     });
 }

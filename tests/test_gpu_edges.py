@@ -138,3 +138,59 @@ def test_misfit_lengths(wave_mod, n):
     assert torch.equal(r, a - b)
     ref = 0.5 * np.sum((a.cpu().numpy().astype(np.float64) - b.cpu().numpy()) ** 2)
     assert abs(J.item() - ref) <= (n + 2) * 2.0 ** -52 * ref
+
+
+# the same kernels on rows of one to three groups, one row of many blocks, and
+# rows shared by blocks that do not divide them
+@pytest.mark.parametrize("dtype", ["f32", "bf16uv"])
+@pytest.mark.parametrize("shape", [(2, 3, 700), (9, 257, 3), (40000, 1, 1), (5003, 2, 3), (261, 1, 9)])
+def test_utility_kernels_on_thin_grids(wave_mod, shape, dtype):
+    nx, ny, nz = shape
+    p = inputs.random_problem(nx, ny, nz, 2, seed=nx, nrec=1)
+    print(f"case: utilities {shape} {dtype}", flush=True)
+    prop = make(wave_mod, p, dtype)
+    cur, _, _ = prop.fields()
+    # integers of a few bits are exact in every storage (scale 2^0 after a reset)
+    vals = torch.randint(-100, 101, (nz, ny, nx), device="cuda", generator=torch.Generator("cuda").manual_seed(nx))
+    prop.interior(cur)[:] = vals.to(prop.interior(cur).dtype)
+    assert torch.equal(prop.export(0), vals.float())
+    prop.traces.view(-1)[-1] = float("inf")
+    assert prop.check() == (0, 0)  # no step yet: no trace rows
+    bad = torch.randperm(nx * ny * nz, generator=torch.Generator().manual_seed(ny))[:17]
+    flat = prop.interior(cur).flatten().clone()
+    flat[bad.cuda()] = float("nan")
+    prop.interior(cur)[:] = flat.view(nz, ny, nx)
+    assert prop.check()[0] == 17
+    prop.close()
+    for at in (0, nx * ny * nz // 2, nx * ny * nz - 1):
+        k = p.k32().copy()
+        k.reshape(-1)[at] = float("nan")
+        with pytest.raises(wave_mod.WaveError):
+            wave_mod.Propagator(nx, ny, nz, p.h, k, dtype=dtype).close()
+
+
+# a pass over a grid's cells takes about as long however they are arranged:
+# rows of few cells use all lanes, few long rows all CUs (launch 64 x 4 threads
+# over rows alone and these take 6 to 20 times the cube's time)
+def test_export_time_does_not_depend_on_the_arrangement(wave_mod):
+    def us(nx, ny, nz):
+        k = torch.full((1, 1, 1), 2.0, device="cuda").expand(nz, ny, nx)
+        prop = wave_mod.Propagator(nx, ny, nz, (10.0, 10.0, 10.0), k)
+        out = torch.zeros_like(prop.buf[0])
+        best = float("inf")
+        for _ in range(10):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(20):
+                wave_mod.wave_export(prop.ctx, 0, out.data_ptr())
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1) * 1e3 / 20)
+        prop.close()
+        return best
+
+    cube = us(128, 128, 128)
+    for shape in ((262144, 2, 4), (524288, 2, 2)):
+        t = us(*shape)
+        print(f"case: export {shape}: {t:.1f} us, cube {cube:.1f}", flush=True)
+        assert t < 4 * cube + 10
