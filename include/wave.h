@@ -234,7 +234,8 @@ int wave_sync(wave_ctx *ctx);
  * (copied; NULL = no source).  Library-owned device memory, kept until the
  * next call or wave_destroy: 2 ceil(nt / C) fields of wave_layout bytes each
  * (none when C >= nt) and C Laplacians of the interior cells, rows padded to
- * a multiple of 128 bytes.
+ * a multiple of 128 bytes; for segments of one or two steps the nt Laplacians
+ * of the run instead, which take less.
  * WAVE_ENOMEM when it cannot be allocated, WAVE_EINVAL for 16-bit storage. */
 int wave_forward_checkpointed(wave_ctx *ctx, int32_t nt, const float *src_dev, int32_t every);
 
@@ -285,8 +286,9 @@ int wave_velocity_to_k(const float *v_dev, int64_t n, double dt, float *k_dev, v
  * cross-check. */
 int wave_set_adjoint_fusion(wave_ctx *ctx, int32_t on);
 
-/* Steps, segment length, segments and bytes of checkpoint/Laplacian storage of
- * the last checkpointed forward run (nt = 0 when there is none). */
+/* Steps, segment length (as asked, or chosen), segments and bytes of
+ * checkpoint/Laplacian (and source value) storage of the last checkpointed
+ * forward run (nt = 0 when there is none). */
 int wave_grad_info(const wave_ctx *ctx, int32_t *nt, int32_t *every, int32_t *segments, int64_t *bytes);
 
 /* Least-squares misfit of n trace values: *misfit_dev = 0.5 sum (t - d)^2,

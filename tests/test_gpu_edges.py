@@ -194,3 +194,38 @@ def test_export_time_does_not_depend_on_the_arrangement(wave_mod):
         t = us(*shape)
         print(f"case: export {shape}: {t:.1f} us, cube {cube:.1f}", flush=True)
         assert t < 4 * cube + 10
+
+
+# segments of one or two steps: the same gradient as with every Laplacian kept,
+# in no more memory and without recomputing the steps (a recomputed step costs
+# about as much as the adjoint step it serves)
+@pytest.mark.parametrize("every", [1, 2])
+def test_short_segments_recompute_nothing(wave_mod, every):
+    nt = 21
+    p = inputs.random_problem(203, 181, 157, nt, seed=5, sponge_width=6, nrec=20)
+    tg = torch.tensor(np.random.default_rng(9).standard_normal((nt, len(p.rec))), dtype=torch.float32, device="cuda")
+    got = {}
+    for e in (0, every):
+        print(f"case: gradient 203x181x157 nt {nt} every {e}", flush=True)
+        prop = make(wave_mod, p)
+        for b, seed in zip(prop.fields()[:2], (1, 2)):  # a wave field everywhere from the first level on
+            gen = torch.Generator(device="cuda").manual_seed(seed)
+            prop.interior(b)[:] = torch.randn((p.nz, p.ny, p.nx), device="cuda", generator=gen)
+        prop.forward_checkpointed(nt, src_of(p), e)
+        grads = [prop.adjoint(tg).cpu().numpy() for _ in range(2)]
+        assert np.array_equal(*grads)
+        times = []
+        for _ in range(7):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            prop.adjoint(tg)
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1))
+        got[e] = grads[0], prop.grad_info(), min(times)
+        prop.close()
+    assert np.abs(got[0][0]).max() > 0 and np.array_equal(got[0][0], got[every][0])
+    assert got[every][1][:3] == (nt, every, -(-nt // every))
+    assert got[every][1][3] <= got[0][1][3]
+    print(f"case: adjoint run {got[every][2]:.3f} ms, {got[0][2]:.3f} with every Laplacian asked for", flush=True)
+    assert got[every][2] < 1.3 * got[0][2]
