@@ -448,11 +448,13 @@ constexpr int kPlan16Small = 2, kPlan16Large = 12;  // t64x16_r1, t128x32_r2
 constexpr Plan16 kPlan16[2][2] = {{{kPlan16Small, 1.20, 0.50}, {kPlan16Large, 1.41, 0.10}},   // two levels
                                   {{kPlan16Small, 1.44, 0.50}, {kPlan16Large, 1.70, 0.25}}};  // u and change
 
+// The choice for chunks of *zc planes, or with *zc = 0 of the chunk too (256^3
+// FP16 in chunks of 64: 46 us; with the shape of the library's own chunk, 80).
 int plan16(int nx, int ny, int nz, int kind, int *zc)
 {
     double best = 0.0;
     int v = kPlan16Large;
-    *zc = nz;
+    const int given = std::min(*zc, nz);
     for (const Plan16 &p : kPlan16[is_uv(kind) ? 1 : 0]) {
         const Variant &V = kVariants[p.v];
         const int tx = 4 * V.txv, tyr = V.ty * V.ry;
@@ -460,8 +462,8 @@ int plan16(int nx, int ny, int nz, int kind, int *zc)
         int cus = 0;
         const int per_cu = fit_per_cu(kind, p.v, &cus);
         const long long cap = (long long)cus * (p.v == kPlan16Large ? 1 : std::min(per_cu, 3));
-        for (int c = 1; c <= nz; ++c) {
-            const int z = (nz + c - 1) / c;
+        for (int c = 1; c <= (given > 0 ? 1 : nz); ++c) {
+            const int z = given > 0 ? given : (nz + c - 1) / c;
             if (c > 1 && z == (nz + c - 2) / (c - 1))
                 continue;  // the same chunk length as c - 1
             const long long nwg = tiles * ((nz + z - 1) / z);
@@ -512,10 +514,7 @@ Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
         // 16-bit.  Two levels on grids of 2^27 cells or more take 128 x 16
         // tiles of two rows in two work-groups per CU: BF16 512^3 187 us
         // against 195 with 128 x 32 (FP16 205 against 194)
-        int z = nz;
-        v = !is_uv(kind) && cells >= (1ll << 27) ? kAuto16Variant : plan16(nx, ny, nz, kind, &z);
-        if (zc <= 0 && v != kAuto16Variant)
-            zc = z;
+        v = !is_uv(kind) && cells >= (1ll << 27) ? kAuto16Variant : plan16(nx, ny, nz, kind, &zc);
     }
     g.v = v;
     if (v == kNaive) {

@@ -39,3 +39,31 @@ def test_plan_matches_naive_kernel(wave_mod, shape, dtype):
     assert name in ("t64x16_r1", "t128x32_r2")
     cap = torch.cuda.get_device_properties(0).multi_processor_count * (3 if name == "t64x16_r1" else 1)
     assert wg / (-(-wg // cap) * cap) > 0.6
+
+
+# a z-chunk given with the tile shape left to the library: the shape is chosen
+# for that chunk, not for the one the library would have taken
+@pytest.mark.parametrize("shape,zc", [((256, 256, 256), 64), ((256, 256, 256), 256), ((512, 512, 256), 256)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16uv"])
+def test_tile_shape_fits_a_given_chunk(wave_mod, shape, zc, dtype):
+    nx, ny, nz = shape
+    k = torch.full((1, 1, 1), 2.0, device="cuda").expand(nz, ny, nx)
+    prop = wave_mod.Propagator(nx, ny, nz, (10.0, 10.0, 10.0), k, dtype=dtype)
+    us = {}
+    for variant in (0, "t64x16_r1", "t128x32_r2"):
+        prop.configure(variant, zc)
+        best = float("inf")
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            prop.run(4)
+            e0.record()
+            prop.run(20)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1) * 1e3 / 20)
+        us[variant] = best
+        if variant == 0:
+            assert prop.config()[1] == zc
+    prop.close()
+    print(f"case: {dtype} {shape} chunk {zc}: {us}", flush=True)
+    assert us[0] <= 1.2 * min(us.values())
