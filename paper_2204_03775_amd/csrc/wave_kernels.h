@@ -33,9 +33,19 @@ template <bool CACHED, int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void step_tiled_lap(StepArgs a);
 template <int MODE, int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void adjoint_tiled(StepArgs a);
+// Waves per SIMD the registers of step_batch must allow: four for FP32 tiles of
+// one row whose halo is one group a thread.  They come to 131 registers, three
+// over the 128 four waves have, and 128 cost nothing (no spills): two
+// work-groups of 512 threads a CU instead of one (schedule 0, six shots of
+// 120..300 cells a side in 128 x 16 tiles and eight chunks each, 40 steps:
+// 10.2 -> 8.6 ms).
+constexpr int batch_waves(int kind, int txv, int ty, int ry)
+{
+    return kind == WAVE_F32 && ry == 1 && 8 * txv + 2 * ty <= txv * ty ? 4 : 1;
+}
 template <int KIND, int TXV, int TY, int RY>
-__global__ __launch_bounds__(TXV *TY) void step_batch(const ShotDesc *__restrict__ shots, BatchItems it,
-                                                       int j);
+__global__ __launch_bounds__(TXV *TY, batch_waves(KIND, TXV, TY, RY)) void step_batch(
+    const ShotDesc *__restrict__ shots, BatchItems it, int j);
 template <int KIND, int TXV, int TY, int RY>
 __global__ __launch_bounds__(TXV *TY) void step_batch_run(const ShotDesc *__restrict__ shots, BatchItems it,
                                                            RunSync rs);

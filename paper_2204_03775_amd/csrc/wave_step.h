@@ -1141,8 +1141,8 @@ __device__ __forceinline__ void batch_step_items(const ShotDesc *__restrict__ sh
 // One time step of every shot in a group as a persistent launch: the grid
 // holds as many work-groups as fit on the GPU at once.
 template <int KIND, int TXV, int TY, int RY>
-__global__ __launch_bounds__(TXV *TY) void step_batch(const ShotDesc *__restrict__ shots,
-                                                       BatchItems it, int j)
+__global__ __launch_bounds__(TXV *TY, batch_waves(KIND, TXV, TY, RY)) void step_batch(
+    const ShotDesc *__restrict__ shots, BatchItems it, int j)
 {
     __shared__ int ticket;
     batch_step_items<KIND, TXV, TY, RY>(shots, it, j, ticket);
