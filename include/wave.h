@@ -306,6 +306,8 @@ int wave_misfit(const float *traces_dev, const float *observed_dev, int64_t n, f
  *   ctxs       nshots distinct contexts, configured (wave_configure) before
  *              the batch is created and not reconfigured afterwards; the
  *              naive kernel and u-and-change storage are not batched;
+ *              schedules 0 and 3 may run a shot whose tiling is left to the
+ *              library in a coarser one than it takes alone;
  *   stream     the stream of every batched run (the contexts' own streams
  *              are not used by it); required when use_graph != 0, and then
  *              it must not be the legacy default stream;

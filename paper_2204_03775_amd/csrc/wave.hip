@@ -182,6 +182,16 @@ struct wave_grad_state {
     int cell_v = -1, cell_zc = -1;  // the tiling of cell_wg
 };
 
+// Receivers by work-group of a tiling (one device allocation): work-group i
+// owns entries start[i] .. start[i + 1] - 1 of off (offset in the field) and
+// idx (receiver).
+struct RecTables {
+    void *base = nullptr;
+    int *start = nullptr;
+    long long *off = nullptr;
+    int *idx = nullptr;
+};
+
 struct wave_ctx {
     wave_params_t p;
     wave_layout_t lay;    // layout of the u fields (and of the stored k)
@@ -207,12 +217,10 @@ struct wave_ctx {
     Coefs coefs{};
     // device tables: those that last (one allocation) and those of the
     // launch configuration (another)
-    void *tables = nullptr, *rec_tables = nullptr;
+    void *tables = nullptr;
+    RecTables rec_tables;
     float *gx = nullptr, *gy = nullptr, *gz = nullptr;
     long long *rec_off_all = nullptr;  // receiver offsets in receiver order (naive sampling)
-    int *rec_start = nullptr;
-    long long *rec_off = nullptr;
-    int *rec_idx = nullptr;
     int *ring = nullptr;  // kRingInts: exps[4], padding to a line, then the maxima (16-bit storage)
     // launch configuration
     int variant = 0, zchunk = 0;  // requested (0 = auto)
@@ -479,6 +487,9 @@ int plan16(int nx, int ny, int nz, int kind, int *zc)
     return v;
 }
 
+// Whether at least 95 % of the lanes of 256-wide tiles lie in the grid.
+bool wide_tiles(int nx) { return double(nx) / (256.0 * ((nx + 255) / 256)) >= 0.95; }
+
 Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
 {
     Geo g;
@@ -489,10 +500,10 @@ Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
     if (v == 0 && !large) {
         v = kSmallVariant;
     } else if (v == 0 && kind == WAVE_F32) {
-        // 128 x 16 or 256 x 8 tiles.  Where at least 95 % of a 256-wide
-        // tile's lanes lie in the grid the wide tiles get 2 %: on full tiles,
-        // where both shapes score the same, they are 1.5-3 % faster (512^3:
-        // 323 against 337 us; 256^3: 38.9 against 39.8).
+        // 128 x 16 or 256 x 8 tiles.  Where the wide tiles' lanes are used
+        // they get 2 %: on full tiles, where both shapes score the same, they
+        // are 1.5-3 % faster (512^3: 323 against 337 us; 256^3: 38.9 against
+        // 39.8).
         // Fields streamed from HBM also try 128 x 32 tiles of two rows per
         // thread, which need half the work-groups: where they make a single
         // round of what takes the others more, or the same share of one with
@@ -500,7 +511,7 @@ Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
         // us; 401x800x400: 408 -> 388; 512x700x300: 313 -> 291).  Within
         // three fields of 4 GiB in all: beyond, the plan tests hold the wide
         // tiles (755x994x1000: 2329 us, 2217 with these).
-        const bool wide = double(nx) / (256.0 * ((nx + 255) / 256)) >= 0.95;
+        const bool wide = wide_tiles(nx);
         wave_layout_t lay;
         const bool tall = !fits_in_cache(nx, ny, nz) && wave_layout(nx, ny, nz, WAVE_F32, &lay) == WAVE_OK &&
                           3 * lay.bytes <= (int64_t(1) << 32);
@@ -557,6 +568,19 @@ void plan_launch(wave_ctx *c)
     c->grid = g.grid;
 }
 
+Geo ctx_geo(const wave_ctx *c)
+{
+    Geo g;
+    g.v = c->v_used;
+    g.ntx = c->ntx;
+    g.nty = c->nty;
+    g.nchunks = c->nchunks;
+    g.zc = c->zc_used;
+    g.nwg = c->nwg;
+    g.grid = c->grid;
+    return g;
+}
+
 long long elem_offset(const wave_layout_t &l, int z, int y, int x)
 {
     return ((long long)(z + kGhost) * l.rows + (y + kGhost)) * l.pitch_x + l.x_offset + x;
@@ -601,24 +625,26 @@ T *table_at(void *base, size_t at)
     return reinterpret_cast<T *>(static_cast<char *>(base) + at);
 }
 
-// Per-work-group receiver lists for the tiled kernels.
-int build_receiver_tables(wave_ctx *c)
+void free_tables(RecTables &t)
 {
-    free_dev(c->rec_tables);
-    c->rec_start = c->rec_idx = nullptr;
-    c->rec_off = nullptr;
-    if (c->v_used == kNaive)
-        return WAVE_OK;
-    const Variant &V = kVariants[c->v_used];
+    free_dev(t.base);
+    t = RecTables();
+}
+
+// The context's receivers by work-group of tiling g.
+int build_receiver_tables(wave_ctx *c, const Geo &g, RecTables *t)
+{
+    free_tables(*t);
+    const Variant &V = kVariants[g.v];
     const int tx = 4 * V.txv, tyr = V.ty * V.ry;
-    std::vector<int> start(c->nwg + 1, 0), owner(c->nrec);
+    std::vector<int> start(g.nwg + 1, 0), owner(c->nrec);
     for (int r = 0; r < c->nrec; ++r) {
         const int z = c->rec[3 * r], y = c->rec[3 * r + 1], x = c->rec[3 * r + 2];
-        const int lid = ((z / c->zc_used) * c->nty + y / tyr) * c->ntx + x / tx;
+        const int lid = ((z / g.zc) * g.nty + y / tyr) * g.ntx + x / tx;
         owner[r] = lid;
         start[lid + 1]++;
     }
-    for (int i = 0; i < c->nwg; ++i)
+    for (int i = 0; i < g.nwg; ++i)
         start[i + 1] += start[i];
     std::vector<int> fill(start.begin(), start.end() - 1), idx(std::max(c->nrec, 1));
     std::vector<long long> off(std::max(c->nrec, 1));
@@ -630,12 +656,21 @@ int build_receiver_tables(wave_ctx *c)
     Upload up;
     const size_t at_off = up.add(off.data(), off.size()), at_start = up.add(start.data(), start.size()),
                  at_idx = up.add(idx.data(), idx.size());
-    const int rc = up.send(&c->rec_tables);
+    const int rc = up.send(&t->base);
     if (rc != WAVE_OK)
         return fail(c, WAVE_EHIP, "the receiver tables could not be uploaded");
-    c->rec_off = table_at<long long>(c->rec_tables, at_off);
-    c->rec_start = table_at<int>(c->rec_tables, at_start);
-    c->rec_idx = table_at<int>(c->rec_tables, at_idx);
+    t->off = table_at<long long>(t->base, at_off);
+    t->start = table_at<int>(t->base, at_start);
+    t->idx = table_at<int>(t->base, at_idx);
+    return WAVE_OK;
+}
+
+// The same for the context's own tiling (the naive kernel has none).
+int build_receiver_tables(wave_ctx *c)
+{
+    if (c->v_used != kNaive)
+        return build_receiver_tables(c, ctx_geo(c), &c->rec_tables);
+    free_tables(c->rec_tables);
     return WAVE_OK;
 }
 
@@ -680,9 +715,9 @@ StepArgs make_args(const wave_ctx *c)
     a.src_x = c->src[2];
     a.src_ptr = nullptr;
     a.src_val = 0.f;
-    a.rec_start = c->rec_start;
-    a.rec_off = c->rec_off;
-    a.rec_idx = c->rec_idx;
+    a.rec_start = c->rec_tables.start;
+    a.rec_off = c->rec_tables.off;
+    a.rec_idx = c->rec_tables.idx;
     a.trace_row = (c->traces && c->nrec > 0) ? c->traces + (size_t)c->step * c->nrec : nullptr;
     a.step = int(c->step & 0x3fffffff);
     a.k_scale = c->k_scale;
@@ -801,7 +836,7 @@ void free_device(wave_ctx *c)
     drop_run_graph(c);
     free_grad(c->g);
     free_dev(c->tables);
-    free_dev(c->rec_tables);
+    free_tables(c->rec_tables);
     free_dev(c->k16);
     free_dev(c->dbuf);
 }
@@ -862,19 +897,6 @@ int launch_convert(hipStream_t s, int src_kind, int dst_kind, const void *src, v
 
 // ---------------------------------------------------------------------------
 // gradient with respect to k: checkpointed forward run, adjoint run
-
-Geo ctx_geo(const wave_ctx *c)
-{
-    Geo g;
-    g.v = c->v_used;
-    g.ntx = c->ntx;
-    g.nty = c->nty;
-    g.nchunks = c->nchunks;
-    g.zc = c->zc_used;
-    g.nwg = c->nwg;
-    g.grid = c->grid;
-    return g;
-}
 
 // The adjoint steps use the context's tiling when one was configured, else
 // their own automatic choice, by the FP32 rule over three tile shapes: the
@@ -1086,6 +1108,10 @@ struct wave_batch {
     };
     std::vector<wave_ctx *> ctx;
     std::vector<int> cfg;  // (variant, zchunk, nwg) of every shot at creation
+    // schedules 0, 2 and 3: every shot's tiling (see batch_geo), and its
+    // receivers by work-group where that is not the context's own
+    std::vector<Geo> geo;
+    std::vector<RecTables> rec;
     std::vector<Group> groups;
     hipStream_t stream = nullptr;
     bool use_graph = false;
@@ -1172,6 +1198,37 @@ void batch_free(wave_batch *b)
         free_dev(g.d_desc);
         free_dev(g.d_items);
     }
+    for (RecTables &t : b->rec)
+        free_tables(t);
+}
+
+// The tiling of a shot that shares its launches with others (schedules 0, 2
+// and 3).  The automatic plans cut a shot alone into enough work-groups to
+// fill the GPU; when the batch does that anyway, short chunks only re-read
+// more planes and fill more queues, and a third tile shape is one more launch
+// a step.  So shots of 2^22 cells and more that are left to the library take
+//   - FP32: chunks of at least 32 planes in 256 x 8 tiles, or the better of
+//     these and 128 x 16 tiles on narrow grids.  40 batches of 1..16 shots:
+//     0.89-1.02 times the time with the shots' own plans (four shots of 88 M
+//     cells in all, 30 steps: 10.4 -> 9.4 ms);
+//   - two-level 16-bit: 128 x 16 tiles of two rows, chunks of at least 32
+//     planes, if those (`coarse` counts them) make two rounds or more (beyond
+//     1024: 0.81-0.98 times the time, one batch 1.16; below 600: 0.95-2.3).
+Geo batch_geo(const wave_ctx *c, long long coarse)
+{
+    const wave_params_t &p = c->p;
+    if (c->variant != 0 || c->zchunk != 0 || (long long)p.nx * p.ny * p.nz < (1ll << 22))
+        return ctx_geo(c);
+    if (p.dtype != WAVE_F32)
+        return coarse >= 2 * round_workgroups(p.dtype, kAuto16Variant)
+                   ? plan_geo(p.nx, p.ny, p.nz, p.dtype, kAuto16Variant, 0)
+                   : ctx_geo(c);
+    if (wide_tiles(p.nx))
+        return plan_geo(p.nx, p.ny, p.nz, WAVE_F32, kAutoVariant, 0);
+    const Cand32 cand[] = {{kAutoNarrowVariant, 1.0, false}, {kAutoVariant, 1.0, false}};
+    int zc = 0;
+    const int v = plan32(p.nx, p.ny, p.nz, cand, 2, &zc);
+    return plan_geo(p.nx, p.ny, p.nz, WAVE_F32, v, zc);
 }
 
 // Schedule 2 is switched off: its first run on the GPU did not complete
@@ -1213,16 +1270,16 @@ int build_flow(wave_batch *b)
             for (const int t : order) {
                 if (xcd[t] != x)
                     continue;
-                const wave_ctx *c = b->ctx[g.shots[t]];
+                const Geo &geo = b->geo[g.shots[t]];
                 FlowShot f{};
                 f.desc = t;
-                f.ntx = c->ntx;
-                f.nty = c->nty;
-                f.nch = (c->p.nz + c->zc_used - 1) / c->zc_used;
+                f.ntx = geo.ntx;
+                f.nty = geo.nty;
+                f.nch = geo.nchunks;
                 f.items = f.ntx * f.nty * f.nch;
                 f.base = xcd_items[x];
                 f.done = done;
-                f.zreach = (kGhost + c->zc_used - 1) / c->zc_used;
+                f.zreach = (kGhost + geo.zc - 1) / geo.zc;
                 xcd_items[x] += f.items;
                 done += f.items;
                 fs.push_back(f);
@@ -2238,26 +2295,41 @@ int wave_batch_create(wave_batch **out, wave_ctx *const *ctxs, int32_t nshots, v
     b->stream = static_cast<hipStream_t>(stream);
     b->use_graph = use_graph != 0;
     b->ctx.assign(ctxs, ctxs + nshots);
+    b->rec.resize(nshots);
+    long long coarse = 0;  // work-groups of the 16-bit shots in large tiles
     for (int i = 0; i < nshots; ++i) {
-        const wave_ctx *c = ctxs[i];
+        const wave_params_t &p = ctxs[i]->p;
+        if (p.dtype != WAVE_F32 && (long long)p.nx * p.ny * p.nz >= (1ll << 22))
+            coarse += plan_geo(p.nx, p.ny, p.nz, p.dtype, kAuto16Variant, 0).nwg;
+    }
+    for (int i = 0; i < nshots; ++i) {
+        wave_ctx *c = ctxs[i];
+        const Geo geo = batch_geo(c, coarse);
+        b->geo.push_back(geo);
+        if ((geo.v != c->v_used || geo.zc != c->zc_used) && build_receiver_tables(c, geo, &b->rec[i]) != WAVE_OK) {
+            batch_free(b);
+            delete b;
+            return WAVE_EHIP;
+        }
         b->cfg.insert(b->cfg.end(), {c->v_used, c->zc_used, c->nwg});
         b->points += (long long)c->p.nx * c->p.ny * c->p.nz;
-        b->workgroups += c->nwg;
+        b->workgroups += geo.nwg;
         int gi = -1;
         for (size_t g = 0; g < b->groups.size(); ++g)
-            if (b->groups[g].kind == c->p.dtype && b->groups[g].variant == c->v_used)
+            if (b->groups[g].kind == c->p.dtype && b->groups[g].variant == geo.v)
                 gi = int(g);
         if (gi < 0) {
             b->groups.emplace_back();
             gi = int(b->groups.size()) - 1;
             b->groups[gi].kind = c->p.dtype;
-            b->groups[gi].variant = c->v_used;
+            b->groups[gi].variant = geo.v;
         }
         b->groups[gi].shots.push_back(i);
     }
     int device = 0, cus = 0;
     if (hipGetDevice(&device) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
+        batch_free(b);
         delete b;
         return WAVE_EHIP;
     }
@@ -2271,11 +2343,12 @@ int wave_batch_create(wave_batch **out, wave_ctx *const *ctxs, int32_t nshots, v
         std::vector<double> work;
         for (size_t t = 0; t < g.shots.size(); ++t) {
             const wave_ctx *c = b->ctx[g.shots[t]];
+            const Geo &geo = b->geo[g.shots[t]];
             const int tx = 4 * V.txv, tyr = V.ty * V.ry;
-            for (int lid = 0; lid < c->nwg; ++lid) {
-                const int ix = lid % c->ntx, rest = lid / c->ntx, iy = rest % c->nty, ch = rest / c->nty;
+            for (int lid = 0; lid < geo.nwg; ++lid) {
+                const int ix = lid % geo.ntx, rest = lid / geo.ntx, iy = rest % geo.nty, ch = rest / geo.nty;
                 const int wx = std::min(tx, c->p.nx - ix * tx), wy = std::min(tyr, c->p.ny - iy * tyr);
-                const int wz = std::min(c->zc_used, c->p.nz - ch * c->zc_used);
+                const int wz = std::min(geo.zc, c->p.nz - ch * geo.zc);
                 ishot.push_back(int(t));
                 ilid.push_back(lid);
                 work.push_back(double(wx) * wy * (wz + 8));
@@ -2425,6 +2498,14 @@ int wave_batch_run(wave_batch *b, int32_t nsteps, const float *const *src_dev)
         for (size_t t = 0; t < g.shots.size(); ++t) {
             const wave_ctx *c = b->ctx[g.shots[t]];
             d[t].a = make_args(c);
+            const RecTables &rec = b->rec[g.shots[t]];
+            if (rec.base) {  // the batch's own tiling
+                const Geo &geo = b->geo[g.shots[t]];
+                set_geo(d[t].a, geo.ntx, geo.nty, geo.nchunks, geo.zc, geo.nwg);
+                d[t].a.rec_start = rec.start;
+                d[t].a.rec_off = rec.off;
+                d[t].a.rec_idx = rec.idx;
+            }
             d[t].traces = (c->traces && c->nrec > 0) ? c->traces : nullptr;
             d[t].nrec = c->nrec;
             d[t].n0 = int(n0);

@@ -508,3 +508,50 @@ def test_flow_schedule_rejects_16bit_and_reports_a_failed_wait(wave_mod):
     b.close()
     for pr in props:
         pr.close()
+
+
+# shots of 2^22 cells and more left to the library share launches in coarser
+# tilings than they take alone; sizes, work-groups of the batch on 256 CUs and
+# launch groups (the last shot of the first row is below 2^22 cells)
+AUTO_BATCHES = {
+    "f32": ([(251, 105, 244), (309, 139, 174), (160, 251, 150), (119, 117, 188)], 98 + 243 + 256 + 512, 3),
+    "f16": ([(290, 323, 203), (328, 232, 250), (324, 328, 151), (254, 300, 160)], 378 + 360 + 252 + 190, 1),
+    "bf16": ([(309, 139, 174), (160, 251, 150)], None, 1),  # too few for coarse tilings: the shots' own
+}
+
+
+@pytest.mark.parametrize("dtype", list(AUTO_BATCHES))
+def test_automatic_tilings_of_a_batch(wave_mod, dtype):
+    sizes, workgroups, groups = AUTO_BATCHES[dtype]
+    nt = 5
+    shots = [inputs.random_problem(*n, nt, seed=300 + i, sponge_width=4, nrec=40) for i, n in enumerate(sizes)]
+    auto = [(0, 0)] * len(shots)
+    ref, own = [], 0
+    props, srcs = build(wave_mod, shots, dtype, auto)
+    for pr, s in zip(props, srcs):
+        pr.run(nt, s)
+        pr.sync()
+        ref.append(snapshot(pr))
+        own += pr.config()[2]
+    b = wave_mod.Batch(props, use_graph=True)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert b.info()[:2] == (groups, workgroups or own)
+    for schedule in (0, 3, 1):
+        b.set_schedule(schedule, 2)
+        for rep in range(2):
+            print(f"case: {dtype} automatic tilings, schedule {schedule}, run {rep}", flush=True)
+            for pr in props:
+                pr.reset()
+            b.run(nt, srcs)
+            b.sync()
+            torch.cuda.synchronize()
+            for i, pr in enumerate(props):
+                assert same(snapshot(pr), ref[i]), (schedule, rep, i)
+    b.close()
+    # the contexts keep their own plans and receivers
+    for pr, s, r in zip(props, srcs, ref):
+        pr.reset()
+        pr.run(nt, s)
+        pr.sync()
+        assert same(snapshot(pr), r)
+        pr.close()
