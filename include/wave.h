@@ -392,6 +392,10 @@ int wave_batch_set_wait_limit(wave_batch *b, int32_t polls);
 int wave_batch_info(const wave_batch *b, int32_t *groups, int64_t *workgroups_per_step,
                     int64_t *points_per_step);
 
+/* Schedule 1: how many of the streams asked for get shots (0 with another
+ * schedule). */
+int wave_batch_streams(const wave_batch *b, int32_t *streams);
+
 /* Wait for the batch stream; WAVE_EHIP if a batched launch failed or, with
  * schedule 2 or 3, a dependency or barrier wait gave up. */
 int wave_batch_sync(wave_batch *b);

@@ -127,8 +127,11 @@ const StepKernel kNaiveFn[kNumKinds] = {step_naive<WAVE_F32>, step_naive<WAVE_F1
 // with the step's access pattern: 13 % faster at 256^3 (about 210 MiB),
 // 8-13 % slower at 384^3, where streaming them is better.
 constexpr long long kCacheResidentBytes = 224ll << 20;
-long long step_bytes_touched(int nx, int ny, int nz) { return 3ll * 4 * (nx + 8) * (ny + 8) * (long long)(nz + 8); }
-bool fits_in_cache(int nx, int ny, int nz) { return step_bytes_touched(nx, ny, nz) <= kCacheResidentBytes; }
+long long step_bytes_touched(int nx, int ny, int nz, int kind)
+{
+    return 3ll * elem_bytes(kind) * (nx + 8) * (ny + 8) * (long long)(nz + 8);
+}
+bool fits_in_cache(int nx, int ny, int nz) { return step_bytes_touched(nx, ny, nz, WAVE_F32) <= kCacheResidentBytes; }
 
 // The element encoding of a storage type (the u-and-change types store
 // both of their fields in the encoding of their base type).
@@ -1401,22 +1404,32 @@ int run_enqueue(wave_batch *b, int nsteps)
     return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_EHIP;
 }
 
-// Schedule 1: each shot's steps on one of the K streams with the shot's own
-// kernel; the contexts' bookkeeping advances as the launches are enqueued.
-// The shots of each stream: largest shots first, each to the stream with
-// the least work so far (work = cells per step), so the streams end close
-// together.
-std::vector<std::vector<size_t>> stream_shots(const wave_batch *b)
+// Schedule 1: the streams that get shots, of those asked for.  Shots that run
+// at the same time share the memory-side cache: no more streams than the
+// shots' mean footprint fits it, but two, which hide each launch's ramp and
+// tail behind the other's work (16 FP32 shots of 96..320 cells a side x 60
+// steps, 4 streams asked for: 21.4 ms on all four, 18.9 on two, 20.8 on one;
+// 8 FP16 shots of 320^3 x 40: 15.3 on four, 14.6 on two), and then as many as
+// give every stream the same number of shots (8 FP32 shots of 128^3, 8 streams
+// asked for and 7 by the cache: 1.92 ms on seven, 1.81 on four).
+size_t streams_for(const wave_batch *b, size_t asked)
 {
-    // Shots that run at the same time share the memory-side cache: no more
-    // streams than the shots' mean footprint fits it, but two, which hide
-    // each launch's ramp and tail behind the other's work (16 shots of
-    // 96..320 cells a side x 60 steps, 4 streams asked for: 21.4 ms on all
-    // four, 18.9 on two, 20.8 on one).
+    const size_t n = b->ctx.size();
     double mean = 0.0;
     for (const wave_ctx *c : b->ctx)
-        mean += double(step_bytes_touched(c->p.nx, c->p.ny, c->p.nz)) / double(b->ctx.size());
-    const size_t K = std::min(b->aux.size(), std::max<size_t>(2, size_t(double(kCacheResidentBytes) / mean)));
+        mean += double(step_bytes_touched(c->p.nx, c->p.ny, c->p.nz, c->p.dtype)) / double(n);
+    const size_t cap = std::max<size_t>(2, size_t(double(kCacheResidentBytes) / mean));
+    if (cap >= std::min(asked, n))
+        return std::min(asked, n);
+    const size_t turns = (n + cap - 1) / cap;
+    return (n + turns - 1) / turns;
+}
+
+// The shots of each stream, whose steps run with the shots' own kernels:
+// largest shots first, each to the stream with the least work so far (work =
+// cells per step), so the streams end close together.
+std::vector<std::vector<size_t>> stream_shots(const wave_batch *b)
+{
     std::vector<size_t> order(b->ctx.size());
     for (size_t i = 0; i < order.size(); ++i)
         order[i] = i;
@@ -1426,7 +1439,7 @@ std::vector<std::vector<size_t>> stream_shots(const wave_batch *b)
     };
     std::stable_sort(order.begin(), order.end(),
                      [&](size_t x, size_t y) { return cells(x) > cells(y); });
-    std::vector<double> load(K, 0.0);
+    std::vector<double> load(streams_for(b, b->aux.size()), 0.0);
     std::vector<std::vector<size_t>> out(b->aux.size());
     for (const size_t i : order) {
         const size_t k = std::min_element(load.begin(), load.end()) - load.begin();
@@ -2645,6 +2658,14 @@ int wave_batch_info(const wave_batch *b, int32_t *groups, int64_t *workgroups_pe
         *workgroups_per_step = b->workgroups;
     if (points_per_step)
         *points_per_step = b->points;
+    return WAVE_OK;
+}
+
+int wave_batch_streams(const wave_batch *b, int32_t *streams)
+{
+    if (!b || !streams)
+        return WAVE_EINVAL;
+    *streams = b->schedule == 1 ? int32_t(streams_for(b, b->aux.size())) : 0;
     return WAVE_OK;
 }
 

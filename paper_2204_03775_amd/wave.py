@@ -96,6 +96,7 @@ def _load():
         "wave_batch_set_schedule": ([vp, i32, i32], ci),
         "wave_batch_set_wait_limit": ([vp, i32], ci),
         "wave_batch_info": ([vp, ctypes.POINTER(i32), ctypes.POINTER(i64), ctypes.POINTER(i64)], ci),
+        "wave_batch_streams": ([vp, ctypes.POINTER(i32)], ci),
         "wave_batch_sync": ([vp], ci),
         "wave_batch_destroy": ([vp], ci),
         "wave_batch_last_error": ([vp], ctypes.c_char_p),
@@ -308,6 +309,12 @@ def wave_batch_info(b):
     g, wg, pts = ctypes.c_int32(), ctypes.c_int64(), ctypes.c_int64()
     _bcheck(_lib.wave_batch_info(b, ctypes.byref(g), ctypes.byref(wg), ctypes.byref(pts)), b)
     return g.value, wg.value, pts.value
+
+
+def wave_batch_streams(b) -> int:
+    n = ctypes.c_int32()
+    _bcheck(_lib.wave_batch_streams(b, ctypes.byref(n)), b)
+    return n.value
 
 
 def wave_batch_sync(b):
@@ -558,6 +565,10 @@ class Batch:
     def info(self):
         """(launch groups, work-groups per step, interior points per step)"""
         return wave_batch_info(self.handle)
+
+    def streams(self) -> int:
+        """How many of the streams asked for get shots (schedule 1)."""
+        return wave_batch_streams(self.handle)
 
     def run(self, nsteps: int, srcs=None):
         """``srcs``: one device FP32 tensor (or None) per shot."""

@@ -229,3 +229,37 @@ def test_short_segments_recompute_nothing(wave_mod, every):
     assert got[every][1][3] <= got[0][1][3]
     print(f"case: adjoint run {got[every][2]:.3f} ms, {got[0][2]:.3f} with every Laplacian asked for", flush=True)
     assert got[every][2] < 1.3 * got[0][2]
+
+
+# streams that get shots: what is asked for, while the shots running at once
+# share the memory-side cache (three fields of 4 or 2 bytes a cell), else as
+# many as do, at least two, with as many shots each; FP32 and 16-bit shots on
+# both sides of the limit, the traces those of the shots alone
+@pytest.mark.parametrize("dtype,size,shots,asked,streams", [
+    ("f32", 200, 4, 4, 2), ("f16", 200, 4, 4, 4), ("bf16", 200, 4, 1, 1), ("f16", 290, 3, 3, 2),
+    ("f32", 128, 8, 8, 4), ("f16", 128, 8, 8, 8), ("f32", 96, 3, 16, 3)])
+def test_streams_used(wave_mod, dtype, size, shots, asked, streams):
+    nt = 4
+    p = inputs.random_problem(size, size, size, nt, seed=size, sponge_width=4, nrec=9)
+    alone = make(wave_mod, p, dtype)
+    alone.run(nt, src_of(p))
+    alone.sync()
+    ref = alone.traces.cpu().numpy()
+    alone.close()
+    props = [make(wave_mod, p, dtype) for _ in range(shots)]
+    batch = wave_mod.Batch(props)
+    assert batch.streams() == 0
+    batch.set_schedule(1, asked)
+    print(f"case: {shots} {dtype} shots of {size}^3, {asked} streams asked for: {batch.streams()}", flush=True)
+    assert batch.streams() == streams
+    for _ in range(2):
+        for prop in props:
+            prop.reset()
+        batch.run(nt, [src_of(p)] * shots)
+        batch.sync()
+        torch.cuda.synchronize()
+        for prop in props:
+            assert np.array_equal(prop.traces.cpu().numpy(), ref)
+    batch.close()
+    for prop in props:
+        prop.close()
