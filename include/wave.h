@@ -306,8 +306,8 @@ int wave_misfit(const float *traces_dev, const float *observed_dev, int64_t n, f
  *   ctxs       nshots distinct contexts, configured (wave_configure) before
  *              the batch is created and not reconfigured afterwards; the
  *              naive kernel and u-and-change storage are not batched;
- *              schedules 0 and 3 may run a shot whose tiling is left to the
- *              library in a coarser one than it takes alone;
+ *              a shot whose tiling is left to the library may run in a
+ *              coarser one than it takes alone;
  *   stream     the stream of every batched run (the contexts' own streams
  *              are not used by it); required when use_graph != 0, and then
  *              it must not be the legacy default stream;
@@ -388,7 +388,8 @@ int wave_batch_set_schedule(wave_batch *b, int32_t schedule, int32_t nstreams);
  * a captured graph. */
 int wave_batch_set_wait_limit(wave_batch *b, int32_t polls);
 
-/* Launch groups, work-groups and interior points of one batched step. */
+/* Launch groups (of schedules 0 and 3), and work-groups (in the schedule
+ * set) and interior points of one batched step. */
 int wave_batch_info(const wave_batch *b, int32_t *groups, int64_t *workgroups_per_step,
                     int64_t *points_per_step);
 

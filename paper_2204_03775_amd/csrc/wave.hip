@@ -195,6 +195,12 @@ struct RecTables {
     int *idx = nullptr;
 };
 
+// A tiling for a shot's launches other than its context's own.
+struct Tiling {
+    Geo geo;
+    RecTables rec;
+};
+
 struct wave_ctx {
     wave_params_t p;
     wave_layout_t lay;    // layout of the u fields (and of the stored k)
@@ -695,6 +701,14 @@ void set_geo(StepArgs &a, int ntx, int nty, int nchunks, int zc, int nwg)
     a.mty = multiplier(nty);
 }
 
+void use_tiling(StepArgs &a, const Tiling &t)
+{
+    set_geo(a, t.geo.ntx, t.geo.nty, t.geo.nchunks, t.geo.zc, t.geo.nwg);
+    a.rec_start = t.rec.start;
+    a.rec_off = t.rec.off;
+    a.rec_idx = t.rec.idx;
+}
+
 StepArgs make_args(const wave_ctx *c)
 {
     StepArgs a;
@@ -740,11 +754,13 @@ StepArgs make_args(const wave_ctx *c)
 
 // One forward step from (cur = u^n, prev = u^{n-1}) into `out` (== prev for
 // the in-place step), step counter and trace row as given; lap u^n goes to
-// `lap` if set (FP32).
+// `lap` if set (FP32); in tiling `til` if set, else the context's own.
 int enqueue_forward(wave_ctx *c, void *cur, void *prev, void *out, const float *src_ptr, float src_val,
-                    int64_t step, float *trace_row, void *lap = nullptr)
+                    int64_t step, float *trace_row, void *lap = nullptr, const Tiling *til = nullptr)
 {
     StepArgs a = make_args(c);
+    if (til)
+        use_tiling(a, *til);
     a.cur = cur;
     a.nxt = prev;
     a.out = out;
@@ -757,7 +773,7 @@ int enqueue_forward(wave_ctx *c, void *cur, void *prev, void *out, const float *
         a.dlt = lap;
 
     const int kind = c->p.dtype;
-    if (c->v_used == kNaive) {
+    if (c->v_used == kNaive && !til) {
         hipLaunchKernelGGL(kNaiveFn[kind], dim3(c->grid), dim3(256), 0, c->stream, a);
         if (a.trace_row) {
             const dim3 g((c->nrec + 255) / 256), b(256);
@@ -777,10 +793,10 @@ int enqueue_forward(wave_ctx *c, void *cur, void *prev, void *out, const float *
                                    a.trace_row, ex, slot);
         }
     } else {
-        const Variant &V = kVariants[c->v_used];
+        const Variant &V = kVariants[til ? til->geo.v : c->v_used];
         const StepKernel fn = lap ? V.lap[c->cache_resident ? 1 : 0]
                                   : (c->cache_resident && V.fwd_cached) ? V.fwd_cached : V.fn[kind];
-        hipLaunchKernelGGL(fn, dim3(c->grid), dim3(V.txv * V.ty), 0, c->stream, a);
+        hipLaunchKernelGGL(fn, dim3(til ? til->geo.grid : c->grid), dim3(V.txv * V.ty), 0, c->stream, a);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
@@ -793,10 +809,10 @@ float *trace_row_of(const wave_ctx *c, int64_t step)
     return (c->traces && c->nrec > 0) ? c->traces + (size_t)step * c->nrec : nullptr;
 }
 
-int launch_step(wave_ctx *c, const float *src_ptr, float src_val, void *lap = nullptr)
+int launch_step(wave_ctx *c, const float *src_ptr, float src_val, void *lap = nullptr, const Tiling *til = nullptr)
 {
     const int rc = enqueue_forward(c, c->cur, c->prev, c->prev, src_ptr, src_val, c->step,
-                                   trace_row_of(c, c->step), lap);
+                                   trace_row_of(c, c->step), lap, til);
     if (rc != WAVE_OK)
         return rc;
     // u^{n+1} now lives in the old u^{n-1} buffer
@@ -1111,10 +1127,13 @@ struct wave_batch {
     };
     std::vector<wave_ctx *> ctx;
     std::vector<int> cfg;  // (variant, zchunk, nwg) of every shot at creation
-    // schedules 0, 2 and 3: every shot's tiling (see batch_geo), and its
-    // receivers by work-group where that is not the context's own
-    std::vector<Geo> geo;
-    std::vector<RecTables> rec;
+    // schedules 0, 2 and 3: every shot's tiling (see batch_geo), with its
+    // receivers' tables only where it is not the context's own
+    std::vector<Tiling> til;
+    // schedule 1: every shot's tiling on streams that share the GPU (see
+    // set_stream_tilings), and the number of streams that get shots
+    std::vector<Tiling> stream_til;
+    size_t streams_used = 0;
     std::vector<Group> groups;
     hipStream_t stream = nullptr;
     bool use_graph = false;
@@ -1180,6 +1199,10 @@ void drop_streams(wave_batch *b)
         (void)hipEventDestroy(e);
     b->aux.clear();
     b->ev.clear();
+    for (Tiling &t : b->stream_til)
+        free_tables(t.rec);
+    b->stream_til.clear();
+    b->streams_used = 0;
 }
 
 void drop_flow(wave_batch *b)
@@ -1201,8 +1224,17 @@ void batch_free(wave_batch *b)
         free_dev(g.d_desc);
         free_dev(g.d_items);
     }
-    for (RecTables &t : b->rec)
-        free_tables(t);
+    for (Tiling &t : b->til)
+        free_tables(t.rec);
+}
+
+// The tilings of 16-bit shots of 2^22 cells and more that are left to the
+// library, where they do not run alone: few, large work-groups.
+Geo coarse16_geo(const wave_params_t &p) { return plan_geo(p.nx, p.ny, p.nz, p.dtype, kAuto16Variant, 0); }
+
+bool automatic(const wave_ctx *c)
+{
+    return c->variant == 0 && c->zchunk == 0 && (long long)c->p.nx * c->p.ny * c->p.nz >= (1ll << 22);
 }
 
 // The tiling of a shot that shares its launches with others (schedules 0, 2
@@ -1220,12 +1252,10 @@ void batch_free(wave_batch *b)
 Geo batch_geo(const wave_ctx *c, long long coarse)
 {
     const wave_params_t &p = c->p;
-    if (c->variant != 0 || c->zchunk != 0 || (long long)p.nx * p.ny * p.nz < (1ll << 22))
+    if (!automatic(c))
         return ctx_geo(c);
     if (p.dtype != WAVE_F32)
-        return coarse >= 2 * round_workgroups(p.dtype, kAuto16Variant)
-                   ? plan_geo(p.nx, p.ny, p.nz, p.dtype, kAuto16Variant, 0)
-                   : ctx_geo(c);
+        return coarse >= 2 * round_workgroups(p.dtype, kAuto16Variant) ? coarse16_geo(p) : ctx_geo(c);
     if (wide_tiles(p.nx))
         return plan_geo(p.nx, p.ny, p.nz, WAVE_F32, kAutoVariant, 0);
     const Cand32 cand[] = {{kAutoNarrowVariant, 1.0, false}, {kAutoVariant, 1.0, false}};
@@ -1273,7 +1303,7 @@ int build_flow(wave_batch *b)
             for (const int t : order) {
                 if (xcd[t] != x)
                     continue;
-                const Geo &geo = b->geo[g.shots[t]];
+                const Geo &geo = b->til[g.shots[t]].geo;
                 FlowShot f{};
                 f.desc = t;
                 f.ntx = geo.ntx;
@@ -1425,9 +1455,61 @@ size_t streams_for(const wave_batch *b, size_t asked)
     return (n + turns - 1) / turns;
 }
 
-// The shots of each stream, whose steps run with the shots' own kernels:
-// largest shots first, each to the stream with the least work so far (work =
-// cells per step), so the streams end close together.
+// Schedule 1: the number of streams that get shots, and other tilings than
+// their own for 16-bit shots where several streams run them.  Their own plans
+// fill the GPU with one shot's work-groups, so more streams gain little; the
+// coarse tilings leave room for the others and re-read fewer planes, and the
+// streams need not share the cache: 8 FP16 shots of 200^3 x 40 on four streams
+// take 6.23 ms with their own plans and 5.24 coarse, of 256^3 8.27 and 7.67.
+// That holds where the shots running at once make a round of work-groups
+// (with 200^3 on three streams, 0.91 of a round, the two are even; below, the
+// coarse ones lose up to half) and the coarse tiles' idle lanes do not eat it
+// up: 15 batches of 4..16 shots gained 2-20 % where those tiles hold at most
+// 1.15 times the cells of the shots' own, and lost 4-18 % from 1.19 on.
+int set_stream_tilings(wave_batch *b)
+{
+    const size_t n = b->ctx.size(), K = std::min(b->aux.size(), n);
+    b->streams_used = streams_for(b, b->aux.size());
+    auto tiled_cells = [](const Geo &g, const wave_params_t &p) {
+        const Variant &V = kVariants[g.v];
+        return double(g.ntx) * 4 * V.txv * g.nty * V.ty * V.ry * p.nz;
+    };
+    double own = 0.0, coarse = 0.0, wgs = 0.0;
+    size_t m = 0;
+    for (const wave_ctx *c : b->ctx) {
+        if (c->p.dtype == WAVE_F32)
+            return WAVE_OK;
+        if (automatic(c)) {
+            const Geo g = coarse16_geo(c->p);
+            own += tiled_cells(ctx_geo(c), c->p);
+            coarse += tiled_cells(g, c->p);
+            wgs += g.nwg;
+            ++m;
+        }
+    }
+    if (K < 2 || m == 0 || coarse >= 1.17 * own ||
+        K * (wgs / m) < round_workgroups(b->ctx[0]->p.dtype, kAuto16Variant))
+        return WAVE_OK;
+    b->stream_til.resize(n);
+    for (size_t i = 0; i < n; ++i)
+        if (automatic(b->ctx[i])) {
+            Tiling &t = b->stream_til[i];
+            t.geo = coarse16_geo(b->ctx[i]->p);
+            if (build_receiver_tables(b->ctx[i], t.geo, &t.rec) != WAVE_OK)
+                return WAVE_EHIP;
+        }
+    b->streams_used = K;
+    return WAVE_OK;
+}
+
+// Shot i's tiling in schedule 1: its context's own where this is NULL.
+const Tiling *stream_tiling(const wave_batch *b, size_t i)
+{
+    return !b->stream_til.empty() && b->stream_til[i].rec.base ? &b->stream_til[i] : nullptr;
+}
+
+// The shots of each stream: largest shots first, each to the stream with the
+// least work so far (work = cells per step), so the streams end close together.
 std::vector<std::vector<size_t>> stream_shots(const wave_batch *b)
 {
     std::vector<size_t> order(b->ctx.size());
@@ -1439,7 +1521,7 @@ std::vector<std::vector<size_t>> stream_shots(const wave_batch *b)
     };
     std::stable_sort(order.begin(), order.end(),
                      [&](size_t x, size_t y) { return cells(x) > cells(y); });
-    std::vector<double> load(streams_for(b, b->aux.size()), 0.0);
+    std::vector<double> load(b->streams_used, 0.0);
     std::vector<std::vector<size_t>> out(b->aux.size());
     for (const size_t i : order) {
         const size_t k = std::min_element(load.begin(), load.end()) - load.begin();
@@ -1460,7 +1542,7 @@ int enqueue_stream(wave_batch *b, size_t k, const std::vector<size_t> &shots, in
         const float *src = src_dev ? src_dev[i] : nullptr;
         int rc = WAVE_OK;
         for (int j = 0; j < nsteps && rc == WAVE_OK; ++j)
-            rc = launch_step(c, src ? src + j : nullptr, 0.f);
+            rc = launch_step(c, src ? src + j : nullptr, 0.f, nullptr, stream_tiling(b, i));
         c->stream = saved;
         if (rc != WAVE_OK)
             return rc;
@@ -1512,7 +1594,7 @@ int batch_enqueue_streams(wave_batch *b, int nsteps, const float *const *src_dev
             hipStream_t saved = c->stream;
             c->stream = b->aux[k];
             const float *src = src_dev ? src_dev[i] : nullptr;
-            const int rc = launch_step(c, src ? src + step[k] : nullptr, 0.f);
+            const int rc = launch_step(c, src ? src + step[k] : nullptr, 0.f, nullptr, stream_tiling(b, i));
             c->stream = saved;
             if (rc != WAVE_OK)
                 return rc;
@@ -2308,18 +2390,16 @@ int wave_batch_create(wave_batch **out, wave_ctx *const *ctxs, int32_t nshots, v
     b->stream = static_cast<hipStream_t>(stream);
     b->use_graph = use_graph != 0;
     b->ctx.assign(ctxs, ctxs + nshots);
-    b->rec.resize(nshots);
+    b->til.resize(nshots);
     long long coarse = 0;  // work-groups of the 16-bit shots in large tiles
-    for (int i = 0; i < nshots; ++i) {
-        const wave_params_t &p = ctxs[i]->p;
-        if (p.dtype != WAVE_F32 && (long long)p.nx * p.ny * p.nz >= (1ll << 22))
-            coarse += plan_geo(p.nx, p.ny, p.nz, p.dtype, kAuto16Variant, 0).nwg;
-    }
+    for (int i = 0; i < nshots; ++i)
+        if (ctxs[i]->p.dtype != WAVE_F32 && automatic(ctxs[i]))
+            coarse += coarse16_geo(ctxs[i]->p).nwg;
     for (int i = 0; i < nshots; ++i) {
         wave_ctx *c = ctxs[i];
-        const Geo geo = batch_geo(c, coarse);
-        b->geo.push_back(geo);
-        if ((geo.v != c->v_used || geo.zc != c->zc_used) && build_receiver_tables(c, geo, &b->rec[i]) != WAVE_OK) {
+        const Geo geo = b->til[i].geo = batch_geo(c, coarse);
+        if ((geo.v != c->v_used || geo.zc != c->zc_used) &&
+            build_receiver_tables(c, geo, &b->til[i].rec) != WAVE_OK) {
             batch_free(b);
             delete b;
             return WAVE_EHIP;
@@ -2356,7 +2436,7 @@ int wave_batch_create(wave_batch **out, wave_ctx *const *ctxs, int32_t nshots, v
         std::vector<double> work;
         for (size_t t = 0; t < g.shots.size(); ++t) {
             const wave_ctx *c = b->ctx[g.shots[t]];
-            const Geo &geo = b->geo[g.shots[t]];
+            const Geo &geo = b->til[g.shots[t]].geo;
             const int tx = 4 * V.txv, tyr = V.ty * V.ry;
             for (int lid = 0; lid < geo.nwg; ++lid) {
                 const int ix = lid % geo.ntx, rest = lid / geo.ntx, iy = rest % geo.nty, ch = rest / geo.nty;
@@ -2511,14 +2591,8 @@ int wave_batch_run(wave_batch *b, int32_t nsteps, const float *const *src_dev)
         for (size_t t = 0; t < g.shots.size(); ++t) {
             const wave_ctx *c = b->ctx[g.shots[t]];
             d[t].a = make_args(c);
-            const RecTables &rec = b->rec[g.shots[t]];
-            if (rec.base) {  // the batch's own tiling
-                const Geo &geo = b->geo[g.shots[t]];
-                set_geo(d[t].a, geo.ntx, geo.nty, geo.nchunks, geo.zc, geo.nwg);
-                d[t].a.rec_start = rec.start;
-                d[t].a.rec_off = rec.off;
-                d[t].a.rec_idx = rec.idx;
-            }
+            if (const Tiling &til = b->til[g.shots[t]]; til.rec.base)  // not the context's own
+                use_tiling(d[t].a, til);
             d[t].traces = (c->traces && c->nrec > 0) ? c->traces : nullptr;
             d[t].nrec = c->nrec;
             d[t].n0 = int(n0);
@@ -2642,6 +2716,10 @@ int wave_batch_set_schedule(wave_batch *b, int32_t schedule, int32_t nstreams)
             }
             b->ev.push_back(e);
         }
+        if (set_stream_tilings(b) != WAVE_OK) {
+            drop_streams(b);
+            return bfail(b, WAVE_EHIP, "the receiver tables of the streams' tilings could not be uploaded");
+        }
         b->schedule = 1;
     }
     return WAVE_OK;
@@ -2654,8 +2732,16 @@ int wave_batch_info(const wave_batch *b, int32_t *groups, int64_t *workgroups_pe
         return WAVE_EINVAL;
     if (groups)
         *groups = int32_t(b->groups.size());
-    if (workgroups_per_step)
+    if (workgroups_per_step) {
         *workgroups_per_step = b->workgroups;
+        if (b->schedule == 1) {
+            *workgroups_per_step = 0;
+            for (size_t i = 0; i < b->ctx.size(); ++i) {
+                const Tiling *t = stream_tiling(b, i);
+                *workgroups_per_step += t ? t->geo.nwg : b->ctx[i]->nwg;
+            }
+        }
+    }
     if (points_per_step)
         *points_per_step = b->points;
     return WAVE_OK;
@@ -2665,7 +2751,7 @@ int wave_batch_streams(const wave_batch *b, int32_t *streams)
 {
     if (!b || !streams)
         return WAVE_EINVAL;
-    *streams = b->schedule == 1 ? int32_t(streams_for(b, b->aux.size())) : 0;
+    *streams = int32_t(b->streams_used);
     return WAVE_OK;
 }
 

@@ -263,3 +263,39 @@ def test_streams_used(wave_mod, dtype, size, shots, asked, streams):
     batch.close()
     for prop in props:
         prop.close()
+
+
+# 16-bit shots left to the library on several streams take tilings that leave
+# room for each other where those running at once fill the GPU and the tiles
+# are as full (200 and 230 cells a side: the same lanes along x idle either
+# way), their own where the coarse ones idle more (164) or streams are too few;
+# `coarse`: a shot's work-groups in those tilings on 256 CUs
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("size,streams,coarse", [(200, 4, 156), (230, 3, 210), (164, 4, 0), (200, 2, 0)])
+def test_tilings_of_16bit_shots_on_streams(wave_mod, size, streams, coarse, dtype):
+    nt, shots = 6, 5
+    p = inputs.random_problem(size, size, size, nt, seed=size, sponge_width=6, nrec=30)
+    props = [make(wave_mod, p, dtype) for _ in range(shots)]
+    srcs = [src_of(p)] * shots
+    props[0].run(nt, srcs[0])
+    props[0].sync()
+    ref = state(props[0])
+    own = props[0].config()[2]
+    for graph in (False, True):
+        batch = wave_mod.Batch(props, use_graph=graph)
+        batch.set_schedule(1, streams)
+        print(f"case: {shots} {dtype} shots of {size}^3 on {streams} streams, graph={graph}: "
+              f"{batch.info()[1]} work-groups, {own} a shot alone", flush=True)
+        if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+            assert batch.info()[1] == shots * (coarse or own)
+        for _ in range(2):
+            for prop in props:
+                prop.reset()
+            batch.run(nt, srcs)
+            batch.sync()
+            torch.cuda.synchronize()
+            for prop in props:
+                assert all(np.array_equal(a, b) for a, b in zip(state(prop), ref))
+        batch.close()
+    for prop in props:
+        prop.close()
