@@ -459,7 +459,8 @@ __device__ __forceinline__ void static_for_while(F &&f)
 
 // One work-group's share of a step: the tile and z-chunk numbered `lid`
 // (tiles x fastest, then y, then chunks) of the grid described by `a`.
-template <int KIND, int TXV, int TY, int RY, int MODE = kFwd, bool COH = false, bool CACHED = false>
+// DRAIN: the march starts when every load of the prologue has arrived (see there).
+template <int KIND, int TXV, int TY, int RY, int MODE = kFwd, bool COH = false, bool CACHED = false, bool DRAIN = false>
 __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
 {
     constexpr int NT = TXV * TY;
@@ -766,6 +767,15 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, int lid)
 
     float tmax = 0.f;  // max |stored u^{n+1}| written by this thread (16-bit storage)
     const Coefs c = fd.c;
+    // A batch item's tables and source are read through generic pointers.  With
+    // such a load under way, which either counter may report, the compiler
+    // waits for every load there is: in the march's first plane and, the march
+    // being one loop of ten planes, in every tenth, a full memory latency, 50 ns
+    // a plane.  Waited for here, both counters are known (a shot of 512x256x100
+    // in 256 x 8 tiles of the whole depth: 103.2 -> 95.8 us a step).  16-bit
+    // items wait for them with their scales.
+    if constexpr (DRAIN)
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
     for (int lb = 0; lb < len; lb += QS) {
         static_for_while<0, QS>([&](auto phase) __attribute__((always_inline)) -> bool {
             constexpr int s = decltype(phase)::value;
@@ -1127,7 +1137,7 @@ __device__ __forceinline__ void batch_step_items(const ShotDesc *__restrict__ sh
         int drawn = 0;
         if (early && threadIdx.x == 0)
             drawn = atomicAdd(cnt, 1);
-        tile_step<KIND, TXV, TY, RY>(a, it.lid[item]);
+        tile_step<KIND, TXV, TY, RY, kFwd, false, false, KIND == WAVE_F32>(a, it.lid[item]);
         if (!early && threadIdx.x == 0)
             drawn = atomicAdd(cnt, 1);
         if (threadIdx.x == 0)
