@@ -1245,14 +1245,16 @@ bool automatic(const wave_ctx *c)
 //   - FP32: chunks of at least 32 planes in 256 x 8 tiles, or the better of
 //     these and 128 x 16 tiles on narrow grids.  40 batches of 1..16 shots:
 //     0.89-1.02 times the time with the shots' own plans (four shots of 88 M
-//     cells in all, 30 steps: 10.4 -> 9.4 ms);
+//     cells in all, 30 steps: 10.4 -> 9.4 ms); but a single round of 128 x 32
+//     tiles stays where the batch is that one shot (37 M cells: 4.4 ms against
+//     5.3);
 //   - two-level 16-bit: 128 x 16 tiles of two rows, chunks of at least 32
 //     planes, if those (`coarse` counts them) make two rounds or more (beyond
 //     1024: 0.81-0.98 times the time, one batch 1.16; below 600: 0.95-2.3).
-Geo batch_geo(const wave_ctx *c, long long coarse)
+Geo batch_geo(const wave_ctx *c, long long coarse, bool alone)
 {
     const wave_params_t &p = c->p;
-    if (!automatic(c))
+    if (!automatic(c) || (alone && c->v_used == kTallVariant && p.dtype == WAVE_F32))
         return ctx_geo(c);
     if (p.dtype != WAVE_F32)
         return coarse >= 2 * round_workgroups(p.dtype, kAuto16Variant) ? coarse16_geo(p) : ctx_geo(c);
@@ -2397,7 +2399,7 @@ int wave_batch_create(wave_batch **out, wave_ctx *const *ctxs, int32_t nshots, v
             coarse += coarse16_geo(ctxs[i]->p).nwg;
     for (int i = 0; i < nshots; ++i) {
         wave_ctx *c = ctxs[i];
-        const Geo geo = b->til[i].geo = batch_geo(c, coarse);
+        const Geo geo = b->til[i].geo = batch_geo(c, coarse, nshots == 1);
         if ((geo.v != c->v_used || geo.zc != c->zc_used) &&
             build_receiver_tables(c, geo, &b->til[i].rec) != WAVE_OK) {
             batch_free(b);

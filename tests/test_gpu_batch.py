@@ -517,12 +517,14 @@ AUTO_BATCHES = {
     "f32": ([(251, 105, 244), (309, 139, 174), (160, 251, 150), (119, 117, 188)], 98 + 243 + 256 + 512, 3),
     "f16": ([(290, 323, 203), (328, 232, 250), (324, 328, 151), (254, 300, 160)], 378 + 360 + 252 + 190, 1),
     "bf16": ([(309, 139, 174), (160, 251, 150)], None, 1),  # too few for coarse tilings: the shots' own
+    "f32-alone": ([(755, 994, 60)], None, 1),  # one round of 128 x 32 tiles
 }
 
 
 @pytest.mark.parametrize("dtype", list(AUTO_BATCHES))
 def test_automatic_tilings_of_a_batch(wave_mod, dtype):
     sizes, workgroups, groups = AUTO_BATCHES[dtype]
+    dtype = dtype.split("-")[0]
     nt = 5
     shots = [inputs.random_problem(*n, nt, seed=300 + i, sponge_width=4, nrec=40) for i, n in enumerate(sizes)]
     auto = [(0, 0)] * len(shots)
