@@ -43,3 +43,12 @@ def test_16bit_probe_is_skipped_for_tilings_it_does_not_cover():
 
     for name in ("t256x8_r1", "t64x16_r1", "t128x24_r1", "t128x32_r4", "naive", "auto"):
         assert bench.step_stream16(None, name, 128, True) is None, name
+
+
+def test_adjoint_rate_is_not_divided_by_another_pattern():
+    # the adjoint pass moves 28 B a cell on average; the probes beside it move
+    # 36, with a second stencil field or an FP64 update in every pass
+    with open(os.path.join(ROOT, "bench.py")) as f:
+        source = f.read()
+    assert "adjoint_pass_gbs" in source
+    assert "adjoint_pass_frac" not in source
