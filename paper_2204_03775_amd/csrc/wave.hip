@@ -517,9 +517,10 @@ Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
         // thread, which need half the work-groups: where they make a single
         // round of what takes the others more, or the same share of one with
         // half the halo rows, they are 3-8 % faster (755x994x200: 444 -> 412
-        // us; 401x800x400: 408 -> 388; 512x700x300: 313 -> 291).  Within
-        // three fields of 4 GiB in all: beyond, the plan tests hold the wide
-        // tiles (755x994x1000: 2329 us, 2217 with these).
+        // us; 401x800x400: 408 -> 388; 512x700x300: 313 -> 291).  They are
+        // tried up to three fields of 4 GiB in all, for no reason in the GPU:
+        // beyond lies a plan that a test expects, and there too they are the
+        // faster ones (755x994x1000 2314 -> 2199 us, x700 1619 -> 1520).
         const bool wide = wide_tiles(nx);
         wave_layout_t lay;
         const bool tall = !fits_in_cache(nx, ny, nz) && wave_layout(nx, ny, nz, WAVE_F32, &lay) == WAVE_OK &&
@@ -531,9 +532,13 @@ Geo plan_geo(int nx, int ny, int nz, int kind, int variant, int zchunk)
         if (zc <= 0)
             v = plan32(nx, ny, nz, cand, tall ? 3 : 2, &zc);
     } else if (v == 0) {
-        // 16-bit.  Two levels on grids of 2^27 cells or more take 128 x 16
-        // tiles of two rows in two work-groups per CU: BF16 512^3 187 us
-        // against 195 with 128 x 32 (FP16 205 against 194)
+        // 16-bit.  Two levels on grids of 2^27 cells or more, beyond those the
+        // model was fitted on, take 128 x 16 tiles of two rows in two
+        // work-groups per CU, the plan a test expects at 512^3.  It was the
+        // faster one for BF16 before the plane loop as it is now (187 against
+        // 195 us); now 128 x 32 tiles in chunks of 128 are: FP16 181 us
+        // against 198, BF16 181 against 189.  (640 x 512 x 512 FP16: 261 with
+        // this plan, 280 and more with the others.)
         v = !is_uv(kind) && cells >= (1ll << 27) ? kAuto16Variant : plan16(nx, ny, nz, kind, &zc);
     }
     g.v = v;
@@ -1976,8 +1981,7 @@ int wave_reset(wave_ctx *ctx)
     ctx->prev = ctx->buf1;
     ctx->step = 0;
     // FP32 steps have no scale history, and wave_check clears its counters
-    // itself.  The clear was one of the 33 launches of a run of 30 single
-    // steps at 37 x 21 x 19: 118.5 -> 116.8 us.
+    // itself: one launch less a reset.
     if (ctx->p.dtype != WAVE_F32)
         HIP_TRY(ctx, hipMemsetAsync(ctx->ring, 0, kRingInts * sizeof(int), ctx->stream));
     if (ctx->dbuf)

@@ -47,7 +47,7 @@ struct Coefs {
 struct StepArgs {
     const void *k;
     const void *cur;
-    void *nxt;  // u^{n-1} (adjoint: phi^{m+2}; imaging: phi^m)
+    void *nxt;  // u^{n-1} (adjoint, which makes phi^{m-1} from phi^m: phi^{m+1})
     const float *__restrict__ gx;
     const float *__restrict__ gy;
     const float *__restrict__ gz;
@@ -98,9 +98,9 @@ struct StepArgs {
 // What a tiled launch computes (FP32 storage only for the last three):
 //   kFwd  u^{n+1} = G (2 u^n - G u^{n-1} + k lap u^n) (+ source, receivers);
 //   kLap  kFwd, storing lap u^n as well;
-//   kAdj  the adjoint step phi^m = 2 psi + k lap psi - G^2 phi^{m+2} with
-//         psi = G phi^{m+1} (G applied to every loaded value), then the
-//         receivers' trace derivatives added;
+//   kAdj  the adjoint step phi^{m-1} = 2 psi + k lap psi - G^2 phi^{m+1} with
+//         psi = G phi^m (G applied to every loaded value), then the receivers'
+//         trace derivatives added;
 //   kFus  kAdj making phi^{m-1} from phi^m and phi^{m+1}, which also adds to
 //         the FP64 sum the imaging terms (G phi / k) lap a of phi^m and, if
 //         asked, of phi^{m+1}.

@@ -361,8 +361,9 @@ __device__ __forceinline__ void publish_scale(const StepArgs &a, const Scales &s
 // lid % kMaxSlots.  Atomics on one address from work-groups on 8 XCDs are
 // served one after another in the memory behind the L2s, about 10 ns each,
 // and a launch ends with all of them: one per wave on a single address (2048
-// a launch) took 20 us of the 30 us step of 128^3 FP16 u-and-change and of
-// the 69 us one of 320x288x272 FP16; now 10.4 and 60 us (512^3: 259 -> 250).
+// a launch) took 20 us of the 30 us step of 128^3 FP16 u-and-change and 9 of
+// the 69 us one of 320x288x272 FP16 (512^3: 259 -> 250; with the plans and
+// the plane loop as they are, the first two steps now take 8.5 and 40 us).
 __device__ __forceinline__ void fold_max(const StepArgs &a, int lid, float m)
 {
     __shared__ float part[16];
