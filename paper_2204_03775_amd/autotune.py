@@ -138,6 +138,21 @@ SINGLE_CHUNKS = (0, 8, 16, 32, 64)  # z-chunk (0: the library's automatic choice
 STREAM_COUNTS = (1, 2, 4)
 
 
+def stream_counts(props, stream) -> list:
+    """The stream counts worth timing: of those that give shots to as many
+    streams (the library uses no more than share the memory-side cache) the
+    smallest."""
+    used = {}
+    b = wave.Batch(props, stream=stream, use_graph=True)
+    try:
+        for k in STREAM_COUNTS:
+            b.set_schedule(1, k)
+            used.setdefault(b.streams(), k)
+    finally:
+        b.close()
+    return sorted(used.values())
+
+
 def _single_key(p) -> str:
     return f"{arch()}|{p.dtype}|shot|{p.nx}x{p.ny}x{p.nz}"
 
@@ -188,7 +203,8 @@ def tune_batch(props, srcs, stream, nsteps: int = 30, use_cache: bool = True, lo
     """Choose how to run this batch: schedule 0 (one persistent launch per
     step and group) or schedule 3 (one launch per group for the whole run)
     with a (variant, chunks) per size class, or schedule 1 (every shot with
-    its own tuned configuration on 1, 2 or 4 streams), whichever is fastest.  Configures the Propagators and returns
+    its own tuned configuration on 1, 2 or 4 streams, those that differ),
+    whichever is fastest.  Configures the Propagators and returns
     {"schedule", "nstreams", "classes" or "shots", "us_per_step"}; create
     the Batch afterwards and call its set_schedule(schedule, nstreams).
     Schedule 3 (a cooperative launch) is timed only with
@@ -199,7 +215,8 @@ def tune_batch(props, srcs, stream, nsteps: int = 30, use_cache: bool = True, lo
     t_queue = time_batch(props, srcs, nsteps, stream)
     t_run = time_batch(props, srcs, nsteps, stream, schedule=3) if single_launch else float("inf")
     shots = [tune_single(p, s, stream, use_cache=use_cache, log=log) for p, s in zip(props, srcs)]
-    t_streams = {k: time_batch(props, srcs, nsteps, stream, schedule=1, nstreams=k) for k in STREAM_COUNTS}
+    t_streams = {k: time_batch(props, srcs, nsteps, stream, schedule=1, nstreams=k)
+                 for k in stream_counts(props, stream)}
     k_best = min(t_streams, key=t_streams.get)
     if log:
         log(f"tune batch: schedule 0 {t_queue * 1e6:.1f} us/step; schedule 3 {t_run * 1e6:.1f}; schedule 1 "

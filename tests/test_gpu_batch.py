@@ -557,3 +557,18 @@ def test_automatic_tilings_of_a_batch(wave_mod, dtype):
         pr.sync()
         assert same(snapshot(pr), r)
         pr.close()
+
+
+# stream counts the library runs alike are one candidate: three FP32 shots of
+# 200^3 share the memory-side cache two at a time, of 96^3 all at once
+@pytest.mark.parametrize("size,counts", [(200, [1, 2]), (96, [1, 2, 4])])
+def test_tuner_stream_counts_differ(wave_mod, size, counts):
+    from paper_2204_03775_amd import autotune
+
+    k = torch.full((1, 1, 1), 2.0, device="cuda").expand(size, size, size)
+    props = [wave_mod.Propagator(size, size, size, (10.0, 10.0, 10.0), k) for _ in range(3)]
+    stream = torch.cuda.Stream()
+    print(f"case: stream counts of three shots of {size}^3", flush=True)
+    assert autotune.stream_counts(props, stream) == counts
+    for pr in props:
+        pr.close()
