@@ -2305,7 +2305,8 @@ int count_nonfinite_into(wave_ctx *ctx, int *d, int64_t *field_nonfinite, int64_
     const long long nt = (ctx->traces && ctx->nrec > 0) ? std::min<long long>(ctx->step, ctx->trace_cap) : 0;
     hipLaunchKernelGGL(zero_ints, dim3(1), dim3(64), 0, ctx->stream, d, 2ll);
     RowBlocks rows(ctx->p.nx, ctx->p.ny, ctx->p.nz);
-    rows.grid.x = std::max(rows.grid.x, (unsigned)std::min<long long>((nt * ctx->nrec + 1023) / 1024, 2048));
+    const unsigned for_traces = (unsigned)std::min<long long>((nt * ctx->nrec + 1023) / 1024, 2048);
+    rows.grid.x = std::max(rows.grid.x, (for_traces + rows.grid.y - 1) / rows.grid.y);
     hipLaunchKernelGGL(count_nonfinite, rows.grid, rows.block, 0, ctx->stream, (const void *)ctx->cur, ctx->p.dtype,
                        ctx->p.nx, ctx->p.ny, ctx->p.nz, int(ctx->lay.pitch_x), int(ctx->lay.x_offset),
                        (long long)ctx->lay.plane, (const float *)ctx->traces, nt * ctx->nrec, d);

@@ -299,3 +299,34 @@ def test_tilings_of_16bit_shots_on_streams(wave_mod, size, streams, coarse, dtyp
         batch.close()
     for prop in props:
         prop.close()
+
+
+# the watchdog's count over many trace values takes as long on a grid of few
+# long rows as on a cube (blocks along rows times blocks for the traces made
+# two million of them), and finds the last value
+def test_check_of_many_traces_on_a_thin_grid(wave_mod):
+    def count(nx, ny, nz, nt=2000, nrec=1024):
+        k = torch.full((1, 1, 1), 2.0, device="cuda").expand(nz, ny, nx)
+        prop = wave_mod.Propagator(nx, ny, nz, (10.0, 10.0, 10.0), k,
+                                   rec=[[i % nz, (i // nz) % ny, (7 * i) % nx] for i in range(nrec)])
+        prop.record(nt)
+        prop.run(nt)
+        prop.sync()
+        prop.traces[-1, -1] = float("nan")
+        prop.traces[0, 0] = float("inf")
+        assert prop.check() == (0, 2)
+        best = min(_wall(prop.check) for _ in range(10))
+        prop.close()
+        return best * 1e6
+
+    def _wall(f):
+        import time
+
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        f()
+        return time.perf_counter() - t
+
+    cube, thin = count(100, 100, 100), count(262144, 2, 2)
+    print(f"case: check of 2e6 trace values: cube {cube:.1f} us, 262144x2x2 {thin:.1f} us", flush=True)
+    assert thin < 3 * cube + 20
